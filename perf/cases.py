@@ -1,0 +1,324 @@
+"""The work this library is used for, as cases that can be timed and checked.
+
+A case is one pass through the public entry points (`paper_1808_03843_amd.Als`): a whole ALS sweep (rows, then columns),
+an implicit-feedback sweep, the training RMSE, or the CSC of a matrix from its CSR.  Inputs are seeded synthetic rating
+matrices with the degree skew of the paper's datasets (rank-size law for the rows, Zipf popularity of the columns),
+made on the GPU; `exact` is the same arithmetic in double precision with plain torch.
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_1808_03843_amd as P
+
+DEV = "cuda:0"
+DTYPES = {"f32": (P.F32, torch.float32), "bf16": (P.BF16, torch.bfloat16), "f16": (P.F16, torch.float16),
+          "f32x3": (P.F32X3, torch.float32), "f32x2": (P.F32X2, torch.float32)}
+CG_ITERS = 6          # f_s of the paper's experiments
+
+
+def _case(name, kind, m, n, nnz, f, solver="cg", dtype="f32", ratings="stars", lam=0.05, row_s=1.0, col_s=1.0, alpha=0.0):
+    c = {"kind": kind, "m": m, "n": n, "nnz": nnz, "f": f, "solver": solver, "dtype": dtype, "ratings": ratings,
+         "lam": lam, "row_s": row_s, "col_s": col_s, "alpha": alpha}
+    return dict({"name": name}, **c) if name else c
+
+
+def listed():
+    return [
+        # the smallest call: the tiny workload of the tests and the smoke run; launches and latency decide
+        _case("tiny_exact", "sweep", 2_000, 1_000, 60_000, 16, solver="exact", row_s=1.1, col_s=0.8),
+        # a small catalogue refitted often with the paper's solver (the reduced Mid shape of the tests)
+        _case("small_cg", "sweep", 12_000, 2_400, 1_500_000, 100),
+        # a small square matrix, ratings on a scale of 100, exact solver (the reduced Large-square shape)
+        _case("square_small_exact", "sweep", 9_000, 7_000, 600_000, 100, solver="exact", ratings="percent", lam=1.0, col_s=1.1),
+        # the Netflix-shaped workload of bench.py: CG with fp32 factors, the default options
+        _case("mid_cg", "sweep", 480_189, 17_770, 99_072_112, 100),
+        # the YahooMusic-shaped workload, both sides wide, with bf16 factor inputs (the conversion is part of the sweep)
+        _case("large_square_cg_bf16", "sweep", 1_000_990, 624_961, 252_800_275, 100, dtype="bf16", ratings="percent", lam=1.0, col_s=1.1),
+        # the paper's baseline solver on a mid-sized matrix of odd sizes
+        _case("mid_exact", "sweep", 120_047, 17_771, 24_768_001, 100, solver="exact"),
+        # many users with few ratings each (the Hugewiki regime: half the rows below 16 entries), two-part fp32 inputs
+        _case("tall_cg_f32x2", "sweep", 2_000_003, 20_011, 80_000_000, 100, dtype="f32x2", row_s=1.0),
+        # the wide end of the factor-width sweep
+        _case("wide_cg", "sweep", 120_047, 17_770, 24_768_028, 256),
+        # the narrow end of the factor-width sweep, fp16 inputs, odd sizes
+        _case("narrow_cg_f16", "sweep", 300_007, 12_345, 40_000_003, 32, dtype="f16"),
+        # implicit feedback (Section 5.6): counts, confidence scale 2
+        _case("implicit_cg", "implicit", 120_047, 17_770, 24_768_028, 100, ratings="counts", alpha=2.0),
+        # the metric after a sweep on the Netflix-shaped workload
+        _case("mid_rmse", "rmse", 480_189, 17_770, 99_072_112, 100),
+        # the index work when a matrix is loaded: CSC from CSR
+        _case("mid_transpose", "transpose", 480_189, 17_770, 99_072_112, 100),
+    ]
+
+
+def draw(rng):
+    """One more case of the same ranges: shape, skew, width, solver, element type and kind of call all drawn."""
+    def logint(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    kind = rng.choice(["sweep"] * 7 + ["implicit", "rmse", "transpose"])
+    f = rng.choice([16, 32, 64, 100, 100, 100, 128, 256])
+    dtype = rng.choice(["f32", "f32", "f32", "bf16", "f16", "f32x3", "f32x2"])
+    if (f == 256 and dtype in ("f32x3", "f32x2")) or kind in ("rmse", "transpose"):
+        dtype = "f32"
+    if kind == "implicit" and (dtype in ("f32x3", "f32x2") or f == 256):
+        dtype = "f32"
+    m = logint(1_000, 500_000)
+    n = logint(500, max(1_000, m))
+    mean = math.exp(rng.uniform(math.log(8), math.log(300)))
+    nnz = int(min(m * mean, 0.2 * m * n, 60_000_000, 99_072_112 * (100 / f) ** 2 * 0.5))
+    ratings = "counts" if kind == "implicit" else rng.choice(["stars", "stars", "percent"])
+    return _case(None, kind, m, n, nnz, f, solver=rng.choice(["cg", "cg", "exact"]), dtype=dtype, ratings=ratings,
+                 lam=1.0 if ratings == "percent" else rng.choice([0.05, 0.1]), row_s=rng.choice([0.6, 1.0, 1.1]),
+                 col_s=rng.choice([0.6, 0.8, 1.0, 1.1]), alpha=rng.choice([1.0, 2.0, 10.0]) if kind == "implicit" else 0.0)
+
+
+# ---- inputs ------------------------------------------------------------------------------------------------------
+def _degrees(case, extra=1.0):
+    """Row degrees before the seeded shuffle: the rank-size law clip(C (i+1)^-s, 1, min(0.95 n, 60000)) with sum ~ extra nnz."""
+    law = np.arange(1, case["m"] + 1, dtype=np.float64) ** -case["row_s"]
+    cap = max(1.0, min(0.95 * case["n"], 60_000.0))
+    lo, hi, want = 0.0, float(case["nnz"]) * 1e3, extra * case["nnz"]
+    for _ in range(80):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if np.clip(mid * law, 1.0, cap).sum() < want else (lo, mid)
+    return np.rint(np.clip(hi * law, 1.0, cap)).astype(np.int64)
+
+
+def _matrix(case, seed):
+    """Canonical CSR on the GPU: (ptr int32, idx int32, val float32).  Row u takes its columns from d_u equal strata of
+    the popularity distribution (capped at one per row), one draw per stratum; columns drawn twice are dropped, and of
+    the rest every k-th entry or so, until exactly nnz are left."""
+    m, n = case["m"], case["n"]
+    g = torch.Generator(device=DEV).manual_seed(seed * 7919 + 11)
+    deg = torch.from_numpy(_degrees(case, 1.12)).to(DEV)[torch.randperm(m, device=DEV, generator=g)]
+    pop = torch.arange(1, n + 1, device=DEV, dtype=torch.float64) ** -case["col_s"]
+    ids = torch.randperm(n, device=DEV, generator=g)
+    key = torch.empty(int(deg.sum()), dtype=torch.int64, device=DEV)
+    at = 0
+    for b in range(20):   # rows by power of two of the degree: they share one capped distribution
+        rows = torch.nonzero((deg >= 2 ** b) & (deg < 2 ** (b + 1))).flatten()
+        if rows.numel() == 0:
+            continue
+        d = deg[rows]
+        top, share = float(d.double().mean()), pop / pop.sum()
+        for _ in range(20):
+            share = torch.clamp(share, max=1.0 / top)
+            share = share / share.sum()
+        cdf = torch.cumsum(share, 0)
+        cnt = int(d.sum())
+        first = torch.cumsum(d, 0) - d
+        dr = torch.repeat_interleave(d, d)
+        k = torch.arange(cnt, device=DEV) - torch.repeat_interleave(first, d)
+        w = (k.double() + torch.rand(cnt, device=DEV, generator=g, dtype=torch.float32).double()) / dr
+        col = torch.searchsorted(cdf, w.clamp_(max=1.0 - 1e-9)).clamp_(max=n - 1)
+        key[at:at + cnt] = torch.repeat_interleave(rows, d) * n + ids[col]
+        at += cnt
+        del dr, k, w, col
+    key = torch.unique_consecutive(torch.sort(key)[0])
+    spare = key.numel() - case["nnz"]
+    if spare < 0:
+        raise ValueError("too many columns drawn twice")
+    if spare > 0:
+        keep = torch.ones(key.numel(), dtype=torch.bool, device=DEV)
+        keep[torch.div(torch.arange(spare, device=DEV) * key.numel(), spare, rounding_mode="floor")] = False
+        key = key[keep]
+    row, idx = torch.div(key, n, rounding_mode="floor"), key % n
+    del key
+    ptr = torch.zeros(m + 1, dtype=torch.int64, device=DEV)
+    ptr[1:] = torch.cumsum(torch.bincount(row, minlength=m), 0)
+    X, T = _factors(case, seed)
+    val = torch.empty(idx.numel(), device=DEV)
+    for s in range(0, idx.numel(), 1 << 22):
+        e = min(idx.numel(), s + (1 << 22))
+        z = (X[row[s:e]] * T[idx[s:e]]).sum(1) + 0.5 * torch.randn(e - s, device=DEV, generator=g)
+        if case["ratings"] == "stars":
+            val[s:e] = torch.clamp(torch.round(3 + z), 1, 5) - 3
+        elif case["ratings"] == "percent":
+            val[s:e] = 10.0 * torch.clamp(torch.round(5 + 2 * z), 0, 10) - 50
+        else:
+            val[s:e] = torch.clamp(torch.round(torch.exp(z)), 0, 50)
+    return ptr.to(torch.int32), idx.to(torch.int32), val
+
+
+def _factors(case, seed):
+    """Factors as they are between two sweeps; the ratings are made from them, with noise, and centred (1..5 about 3,
+    0..100 about 50), as they are before a fit without bias terms.  (With a common direction in all rows of a factor,
+    as raw ratings bring it, the six steps of Algorithm 1 amplify fp32 rounding a thousandfold in any order of the sums,
+    and the error against double precision would say nothing about a kernel.)"""
+    g = torch.Generator(device=DEV).manual_seed(seed * 104729 + 5)
+    X = 0.3 * torch.randn(case["m"], case["f"], device=DEV, generator=g)
+    T = 0.3 * torch.randn(case["n"], case["f"], device=DEV, generator=g)
+    return X, T
+
+
+def prepare(case, seed):
+    als = P.Als(case["f"], solver=P.SOLVER_CG if case["solver"] == "cg" else P.SOLVER_CHOLESKY, cg_iters=CG_ITERS,
+                factor_dtype=DTYPES[case["dtype"]][0])
+    csr = P.SparseMatrix(case["m"], case["n"], *_matrix(case, seed))
+    s = {"case": case, "als": als, "csr": csr}
+    if case["kind"] != "transpose":
+        s["X"], s["T"] = _factors(case, seed)
+    if case["kind"] in ("sweep", "implicit"):
+        s["csc"] = als.csr_to_csc(csr)
+    return s
+
+
+def run(state):
+    case, als, csr = state["case"], state["als"], state["csr"]
+    if case["kind"] == "transpose":
+        c = als.csr_to_csc(csr)
+        return {"ptr": c.ptr, "idx": c.idx, "val": c.val}
+    X, T = state["X"], state["T"]
+    if case["kind"] == "rmse":
+        return als.rmse(csr, X, T)
+    t16 = DTYPES[case["dtype"]][1]
+    if case["kind"] == "implicit":
+        als.update_rows_implicit(csr, T if t16 == T.dtype else T.to(t16), case["lam"], case["alpha"], X)
+        als.update_cols_implicit(state["csc"], X if t16 == X.dtype else X.to(t16), case["lam"], case["alpha"], T)
+    else:
+        als.update_rows(csr, T if t16 == T.dtype else T.to(t16), case["lam"], X)
+        als.update_cols(state["csc"], X if t16 == X.dtype else X.to(t16), case["lam"], T)
+    return {"X": X, "Theta": T}
+
+
+# ---- what a pass cannot do without -------------------------------------------------------------------------------
+def work(case):
+    m, n, nnz, f = case["m"], case["n"], float(case["nnz"]), case["f"]
+    if case["kind"] == "transpose":
+        return {"bytes": 16.0 * nnz + 4.0 * (m + n), "flops": 0.0}
+    if case["kind"] == "rmse":
+        return {"bytes": 8.0 * nnz + 4.0 * m + 4.0 * f * (m + n), "flops": nnz * (2 * f + 3)}
+    gathered = DTYPES[case["dtype"]][1].itemsize
+    # both compressed forms, each factor gathered once and written once, warm starts
+    size = 16.0 * nnz + 4.0 * (m + n) + (m + n) * f * (gathered + 4.0 + (4.0 if case["solver"] == "cg" else 0.0))
+
+    def half(deg):
+        solve = 2.0 * f * f * (CG_ITERS + 1) if case["solver"] == "cg" else f ** 3 / 3.0 + 2.0 * f * f
+        dense = deg * f * (f + 3.0) + solve                      # lower triangle of A_u, b_u, the solver
+        if case["solver"] == "cg" and case["kind"] == "sweep":   # Algorithm 1 on the gathered rows of a short row
+            dense = np.where(deg < 64, np.minimum(dense, (4.0 * (CG_ITERS + 1) + 2.0) * deg * f), dense)
+        elif case["solver"] == "exact" and case["kind"] == "sweep":   # the n_u x n_u system of a short row
+            dense = np.where(deg < f, np.minimum(dense, deg * deg * f + deg ** 3 / 3.0 + 4.0 * deg * f), dense)
+        return float(dense.sum())
+    rows = _degrees(case).astype(np.float64)
+    pop = np.arange(1, n + 1, dtype=np.float64) ** -case["col_s"]
+    cols = np.minimum(pop / pop.sum() * nnz, m)
+    flops = half(rows) + half(cols)
+    if case["kind"] == "implicit":
+        flops += (m + n) * f * (f + 1.0)
+    return {"bytes": size, "flops": flops}
+
+
+def tolerance(case):
+    """About four times and more what the sums of the listed and of drawn cases are off from double precision."""
+    if case["kind"] == "transpose":
+        return "exact"
+    if case["kind"] == "rmse":
+        return {"rel": 1e-6}                     # measured below 1e-8: fp32 dots, fp64 sum over the entries
+    if case["dtype"] in ("bf16", "f16"):         # measured 2e-6 .. 1e-5: some values of X round the other way
+        return {"rel": 1e-4, "max": 1e-2}
+    return {"rel": 1e-5, "max": 2e-3}            # measured 2e-7 .. 2e-6
+
+
+# ---- the same in double precision, plain torch -------------------------------------------------------------------
+def _transpose64(case, ptr, idx, val):
+    rows = torch.repeat_interleave(torch.arange(case["m"], device=DEV), (ptr[1:] - ptr[:-1]).long())
+    order = torch.sort(idx.long(), stable=True)[1]
+    cptr = torch.zeros(case["n"] + 1, dtype=torch.int64, device=DEV)
+    cptr[1:] = torch.cumsum(torch.bincount(idx.long(), minlength=case["n"]), 0)
+    return cptr.to(torch.int32), rows[order].to(torch.int32), val[order]
+
+
+def _solve64(A, b, x, iters, tol):
+    """Algorithm 1 from the warm start x; iterations stop early only where the residual has vanished."""
+    def mul(p):
+        return torch.bmm(A, p.unsqueeze(2)).squeeze(2)
+    r = b - mul(x)
+    p, rs = r.clone(), (r * r).sum(1)
+    floor = tol * tol * (b * b).sum(1) + 1e-300
+    for _ in range(iters):
+        live = rs > floor
+        if not bool(live.any()):
+            break
+        ap = mul(p)
+        a = torch.where(live, rs / (p * ap).sum(1).clamp(min=1e-300), 0.0).unsqueeze(1)
+        x = x + a * p
+        r = r - a * ap
+        new = (r * r).sum(1)
+        p = r + torch.where(live, new / rs.clamp(min=1e-300), 0.0).unsqueeze(1) * p
+        rs = new
+    return x
+
+
+def _half64(case, ptr, idx, val, G, x0):
+    """One half-sweep in double precision: rows in order of degree, A_u from pieces of at most `piece` entries."""
+    f, out = case["f"], torch.zeros_like(x0)
+    deg = (ptr[1:] - ptr[:-1]).long()
+    sorted_deg, order = torch.sort(deg)
+    host = sorted_deg.cpu().numpy()
+    implicit, gram = case["kind"] == "implicit", None
+    if implicit:
+        gram = torch.zeros(f, f, dtype=torch.float64, device=DEV)
+        for s in range(0, G.shape[0], 1 << 16):
+            gram += G[s:s + (1 << 16)].t().contiguous() @ G[s:s + (1 << 16)]
+    pos, most = int(np.searchsorted(host, 1)), len(host)
+    while pos < most:
+        top = max(int(host[pos]) * 5 // 4, int(host[pos]) + 3)
+        end = min(int(np.searchsorted(host, top, side="right")), pos + max(1, (2 << 30) // (8 * f * f)))
+        u, d = order[pos:end], sorted_deg[pos:end]
+        A = torch.zeros(end - pos, f, f, dtype=torch.float64, device=DEV)
+        b = torch.zeros(end - pos, f, dtype=torch.float64, device=DEV)
+        piece = min(int(host[end - 1]), 2048)
+        per = -(-d // piece)
+        owner = torch.repeat_interleave(torch.arange(end - pos, device=DEV), per)
+        nth = torch.arange(owner.numel(), device=DEV) - torch.repeat_interleave(torch.cumsum(per, 0) - per, per)
+        step = max(1, (1 << 30) // (8 * f * piece))
+        lane = torch.arange(piece, device=DEV)
+        for s in range(0, owner.numel(), step):
+            o = owner[s:s + step]
+            off = nth[s:s + step].unsqueeze(1) * piece + lane
+            ok = off < d[o].unsqueeze(1)
+            e = torch.where(ok, ptr[u[o]].long().unsqueeze(1) + off, 0)
+            g = G[idx[e].long()] * ok.unsqueeze(2)
+            r = torch.where(ok, val[e].double(), 0.0)
+            if implicit:
+                w = case["alpha"] * r.clamp(min=0)
+                r = torch.where(r > 0, 1 + w, 0.0)
+                A.index_add_(0, o, torch.bmm((g * w.unsqueeze(2)).transpose(1, 2).contiguous(), g))
+            else:
+                A.index_add_(0, o, torch.bmm(g.transpose(1, 2).contiguous(), g))
+            b.index_add_(0, o, (g * r.unsqueeze(2)).sum(1))
+        if implicit:
+            A += gram
+            A.diagonal(dim1=1, dim2=2).add_(case["lam"])
+        else:
+            A.diagonal(dim1=1, dim2=2).add_(np.float32(case["lam"]).astype(np.float64) * d.double().unsqueeze(1))
+        cg = case["solver"] == "cg"
+        out[u] = _solve64(A, b, x0[u], CG_ITERS if cg else 20 * f, 1e-13 if not cg else 1e-15)
+        pos = end
+    return out
+
+
+def exact(case, seed):
+    ptr, idx, val = _matrix(case, seed)
+    if case["kind"] == "transpose":
+        c = _transpose64(case, ptr, idx, val)
+        return {"ptr": c[0], "idx": c[1], "val": c[2]}
+    X, T = _factors(case, seed)
+    if case["kind"] == "rmse":
+        sse = torch.zeros((), dtype=torch.float64, device=DEV)
+        rows = torch.repeat_interleave(torch.arange(case["m"], device=DEV), (ptr[1:] - ptr[:-1]).long())
+        for s in range(0, idx.numel(), 1 << 23):
+            z = (X[rows[s:s + (1 << 23)]].double() * T[idx[s:s + (1 << 23)].long()].double()).sum(1)
+            sse += (val[s:s + (1 << 23)].double() - z).square().sum()
+        return float(torch.sqrt(sse / idx.numel()))
+    t16 = DTYPES[case["dtype"]][1]
+
+    def gathered(t):   # the factor as the update reads it
+        return t.double() if t16 == torch.float32 else t.to(torch.float32).to(t16).double()
+    X = _half64(case, ptr, idx, val, gathered(T), X.double())
+    cptr, cidx, cval = _transpose64(case, ptr, idx, val)
+    T = _half64(case, cptr, cidx, cval, gathered(X), T.double())
+    return {"X": X, "Theta": T}
