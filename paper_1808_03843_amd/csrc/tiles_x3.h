@@ -7,37 +7,41 @@
 // entries stand against eight fp32 MFMAs (16x16x4) that take twice as long each.
 //
 // Layout as in tiles16.h: one step consumes 32 stored entries, lane (i, kq) supplies its feature of the 8 entries
-// 8kq .. 8kq+7, packed in pairs; the three parts of a value sit at the same place of three operand registers.
-// Rows are gathered entry by entry as fp32 with the lane -> feature map and load widths of the fp32 path.
-// Measured (Mid shape, f = 100): the slot kernel issues 1.3 PFLOP/s of bf16 MFMA work, 94 % of what this chip
-// sustains on back-to-back bf16 MFMAs (it lowers its clock under that load), i.e. 135-155 TFLOP/s of Gram work.
+// 8kq .. 8kq+7, packed in pairs; the parts of a value sit at the same place of two or three operand registers.
 //
-// b_u: when f is not a multiple of 16 the lane i = f % 16 of the last tile carries the fp32 rating instead of a
-// feature and is cut into parts like everything else, so row f of the accumulated matrix is b_u to the same
-// accuracy; the lanes beyond it carry zeros.  When f is a multiple of 16 the three parts of the rating form an
-// operand of their own (lanes 0..2) that is multiplied with all three parts of every tile column: 3 NT more MFMAs
-// per step, whose rows 0..2 add up to b_u.
+// Last tile row (f = 100: 4 features): its A operand stacks the parts, lanes 0-3 the first parts of the 4 features,
+// 4-7 the second, 8-11 the third, and lanes 12 .. the parts of the rating.  Multiplied with each part of a tile column
+// (3 MFMAs instead of 6 with three parts, 2 instead of 3 with two), rows k, 4+k and 8+k of the result add up to row k
+// of the strip and the rows from 12 on add up to b_u, with all part products included.  147 and 77 MFMAs a step
+// instead of 168 and 84.  When f is a multiple of 16 the parts of the rating form an operand of their own (lanes
+// 0..2) that is multiplied with all parts of every tile column, and rows 0..2 of these extra tiles add up to b_u.
 //
 // The gathered rows are staged through LDS (Section 3: the rows of Theta that a row of R refers to are staged on
-// chip in batches; here the staging buffer is a per-wavefront FIFO).
-// Why: the operands of a step (three parts of 32 entries: 84 registers at f = 100) and the 112 accumulator registers
-// leave no room for the 56 registers of the next step's rows in flight if two wavefronts are to share a SIMD -- and
-// with one wavefront per SIMD nothing hides the memory latency or the vector-ALU work of cutting the values into
-// parts.  So the rows of the next step travel by direct global-to-LDS loads (no destination registers), and are read
-// back, 8 registers at a time, just before they are cut.  Every lane reads back exactly what it loaded: the buffer
-// is laid out load instruction by load instruction, lane by lane (bank-conflict free both ways).
-//
-// The buffer of one wavefront holds the rows of one step, in three regions that follow the three kinds of loads of a
-// row (16 bytes per lane for tiles 0 .. 4 N4 - 1; two 4-byte loads for the next 2 N2 tiles; 4 bytes for the last N1
-// tiles).  A region is refilled for step t+1 as soon as step t has read it.
+// chip in batches).  Why: the operands of a step (three parts of 32 entries: 84 registers at f = 100) and the 112
+// accumulator registers leave no room for the 56 registers of the next step's rows in flight if two wavefronts are to
+// share a SIMD -- and with one wavefront per SIMD nothing hides the memory latency or the vector-ALU work of cutting
+// the values into parts.  So the rows of the next step travel by direct global-to-LDS loads (no destination registers).
+// The 32 rows of a step are fetched as one list of 16-byte pieces, 64 consecutive pieces per load instruction, and lie
+// in LDS row after row: f = 100 takes 13 loads instead of the 32 that a lane -> feature map of 16-, 4- and 4-byte loads
+// takes, and every line of a row is asked for once.  The column ids of a step sit in one register (lane l holds entry
+// l % 32) and reach the pieces through the LDS crossbar.  Operands are read back with the lane -> feature map (16, 8
+// and 4 bytes; rows 8 apart start 32 banks apart at f = 100).  The buffer is refilled once the step has read it all;
+// the loads then run under the step's MFMAs.
+// Measured (Mid shape, CG(6), ms per sweep, against the lane-mapped loads): two parts f = 32 4.97 -> 3.51, f = 100
+// 11.6 -> 11.3; three parts f = 100 14.9 -> 14.3; f = 64 and 128 unchanged (their rows were whole 16-byte loads before).
+// Column side at f = 100, two parts: 3.1 ms = the 6.4 TB/s at which rows of X arrive from beyond the L2.
 #pragma once
 #include "tiles16.h"
 
 namespace als {
 
-constexpr int x3_fifo_words(int F) { return 8 * 64 * (4 * loads16(F) + 2 * loads8(F) + loads4(F)); }
+// 16-byte pieces of a row, load instructions per step (64 pieces each), words of the staging buffer
+constexpr int x3_pieces(int F) { return F / 4; }
+constexpr int x3_loads(int F) { return (32 * x3_pieces(F) + 63) / 64; }
+constexpr int x3_fifo_words(int F) { return x3_loads(F) * 256; }
 
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef const __attribute__((address_space(1))) void global_void;
 
 // PARTS = 2 (factor_dtype = ALS_F32X2): the value is cut into two fp16 parts instead, h = fp16(s x) and
@@ -51,7 +55,7 @@ typedef const __attribute__((address_space(1))) void global_void;
 // 2^-25 beside the relative 2^-22.
 //
 // Every wavefront of the kernel must call with its own fifo (x3_fifo_words(F) words, 16-byte aligned).
-template <int F, bool WIDE, bool WANT_B, uint32_t ROWS = rows_all(F), int PARTS = 3>
+template <int F, bool WIDE, bool WANT_B, uint32_t ROWS = rows_all(F), int PARTS = 3, bool FMA_B = false>
 __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ idx, const float *__restrict__ val,
                                                         const void *__restrict__ Theta, int64_t s0, int len,
                                                         v4f (&acc)[tiles_in(ROWS)], float (&b)[tiles_1d(F)],
@@ -70,10 +74,12 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     }
     constexpr int NT = tiles_1d(F), RI = F % 16;
     constexpr bool BX = RI == 0;   // the rating parts are an operand of their own
+    constexpr bool STACK = RI > 0 && RI <= 4;   // last tile row: the parts stacked in one operand (see above)
+    static_assert(BX || STACK, "a partial last tile of more than 4 features is not needed by any supported f");
     constexpr int N4 = loads16(F), N2 = loads8(F), N1 = loads4(F);
     constexpr int base1 = 64 * N4 + 32 * N2, first1 = 4 * N4 + 2 * N2;
     constexpr int LB = (NT - 1) * NT / 2;
-    constexpr int baseA = 0, baseB = 8 * N4 * 256, baseC = baseB + 8 * N2 * 128;   // word offsets of the regions
+    static_assert(F % 4 == 0 && N1 <= 1, "rows are whole 16-byte pieces");
     const int lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
     const int32_t *__restrict__ ib = idx + s0;
     const float *__restrict__ vb = val + s0;
@@ -81,20 +87,11 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     const __amdgpu_buffer_rsrc_t ids_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(ib), 0, 4 * len, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(vb), 0, 4 * len, kRsrcFlags);
     const int nsteps = (len + 31) >> 5;
-    const uint32_t lane_a = 16u * (uint32_t)i;
-    const uint32_t lane_b = 256u * N4 + 8u * (uint32_t)i;
-    const uint32_t lane_c = 4u * (uint32_t)(base1 + i);
-    const uint32_t lane_l = 4u * (uint32_t)((base1 + 16 * (N1 - 1) + i < F) ? base1 + 16 * (N1 - 1) + i : F - 1);
-    const uint32_t lane_first = N4 > 0 ? lane_a : N2 > 0 ? lane_b : N1 > 1 ? lane_c : lane_l;
     const uint32_t eoff0 = 32u * (uint32_t)kq;   // this lane's 8 entries inside a step (bytes into idx / val)
 
-    struct Ids { v4u lo, hi; };
-    auto load_ids = [&](int t) -> Ids {
-        const uint32_t o = eoff0 + 128u * (uint32_t)t;
-        Ids r;
-        r.lo = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ids_rsrc, o, 0, 0));
-        r.hi = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ids_rsrc, o + 16u, 0, 0));
-        return r;
+    // the column id of entry `lane % 32` of a step (beyond the end of the work item: 0, i.e. row 0, read but never used)
+    auto load_ids = [&](int t) -> int {
+        return __builtin_amdgcn_raw_buffer_load_b32(ids_rsrc, 4u * (uint32_t)(lane & 31) + 128u * (uint32_t)t, 0, 0);
     };
     auto load_ratings = [&](int t, float (&r)[8]) {
         if constexpr (!WANT_B) return;
@@ -107,57 +104,44 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
             r[4 + j] = bits_to_float(c[j]);
         }
     };
-    auto row_base = [&](uint32_t c, const char *&p, uint32_t &ro) {
-        if constexpr (WIDE) {
-            p = reinterpret_cast<const char *>(Theta) + (int64_t)c * (4 * F);
-            ro = lane_first;
-        } else {
-            p = reinterpret_cast<const char *>(Theta);
-            ro = row_offset<(uint32_t)(4 * F)>(c, lane_first);
+    lds_u32 *const lds = (lds_u32 *)fifo;
+    // the factor matrix as one buffer with 32-bit offsets (WIDE = false: it is smaller than 4 GiB)
+    const __amdgpu_buffer_rsrc_t theta_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(Theta), 0, (int)0xffffffffu, kRsrcFlags);
+    // the 32 rows of a step, global -> LDS: piece p = 64 k + lane of the step is piece p % CH of entry p / CH
+    constexpr int CH = x3_pieces(F), NI = x3_loads(F);
+    auto dma_rows = [&](int ids) {
+        uint32_t ln = (uint32_t)lane;
+        if constexpr (WIDE) asm volatile("" : "+v"(ln));   // 64-bit addresses: no registers for the entry of every piece
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            const uint32_t piece = 64u * (uint32_t)k + ln;
+            const uint32_t e = piece / (uint32_t)CH, col = piece - e * (uint32_t)CH;
+            // (f = 100: the second half of the last instruction is beyond the step: it fetches the last row once more)
+            const uint32_t c = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (int)(e < 32u ? e : 31u), ids);
+#if defined(__HIP_DEVICE_COMPILE__)   // (the host pass does not know the 16-byte forms)
+            if constexpr (WIDE)
+                __builtin_amdgcn_global_load_lds((global_void *)(reinterpret_cast<const char *>(Theta) + (int64_t)(int)c * (4 * F) + 16u * col),
+                                                 (lds_void *)(lds + 256 * k), 16, 0, 0);
+            else
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(theta_rsrc, (lds_void *)(lds + 256 * k), 16, row_offset<(uint32_t)(4 * F)>(c, 16u * col), 0, 0, 0);
+#endif
         }
     };
-    // the loads of group G (0: 16-byte, 1: the 8-byte pair as two 4-byte loads, 2: 4-byte) of entry j, global -> LDS
-    auto dma_group = [&](auto gtag, int j, uint32_t c) {
-        constexpr int G = decltype(gtag)::value;
-        const char *p;
-        uint32_t ro;
-        row_base(c, p, ro);
-        if constexpr (G == 0 && N4 > 0) {
-            const uint32_t o = ro + (lane_a - lane_first);
-#pragma unroll
-            for (int q = 0; q < N4; ++q)
-                __builtin_amdgcn_global_load_lds((global_void *)(p + o + 256 * q), (lds_void *)(fifo + baseA + (j * N4 + q) * 256), 16, 0, 0);
-        }
-        if constexpr (G == 1 && N2 > 0) {
-            const uint32_t o = ro + (lane_b - lane_first);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-                __builtin_amdgcn_global_load_lds((global_void *)(p + o + 4 * hh), (lds_void *)(fifo + baseB + (j * 2 + hh) * 64), 4, 0, 0);
-        }
-        if constexpr (G == 2 && N1 > 0) {
-            if constexpr (N1 > 1) {
-                const uint32_t o = ro + (lane_c - lane_first);
-#pragma unroll
-                for (int k = 0; k < N1 - 1; ++k)
-                    __builtin_amdgcn_global_load_lds((global_void *)(p + o + 64 * k), (lds_void *)(fifo + baseC + (j * N1 + k) * 64), 4, 0, 0);
-            }
-            __builtin_amdgcn_global_load_lds((global_void *)(p + (ro + (lane_l - lane_first))),
-                                             (lds_void *)(fifo + baseC + (j * N1 + N1 - 1) * 64), 4, 0, 0);
-        }
-    };
-    auto dma8_group = [&](auto gtag, const Ids &ids) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            dma_group(gtag, j, ids.lo[j]);
-            dma_group(gtag, 4 + j, ids.hi[j]);
-        }
-    };
+
     using G0 = std::integral_constant<int, 0>;
     using G1 = std::integral_constant<int, 1>;
     using G2 = std::integral_constant<int, 2>;
 
-    const bool is_rating = i == RI, is_feat = i < RI;
+    // STACK: lanes 0-3, 4-7, 8-11 carry the first, second and third part of the features (two parts: lanes 8-11 zero),
+    // lane 12 + k part k of the rating, the others zero
+    const int part = i < 12 ? i >> 2 : i - 12;
+    const bool is_rating = !FMA_B && i >= 12 && part < PARTS, is_feat = i < 4 * PARTS && (i & 3) < RI;
+    const bool part1 = part == 1, part2 = part == 2;
     const bool is_r0 = i == 0, is_r1 = i == 1, is_r2 = i == 2;
+    float bacc[FMA_B ? NT : 1];   // FMA_B: this lane's share of b_u
+#pragma unroll
+    for (int T = 0; T < (FMA_B ? NT : 1); ++T) bacc[T] = 0.f;
     v4f bt[BX ? NT : 1];   // BX: rows 0..2 of these tiles are the three parts of b_u
 #pragma unroll
     for (int T = 0; T < (BX ? NT : 1); ++T) bt[T] = (v4f){0.f, 0.f, 0.f, 0.f};
@@ -165,10 +149,14 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     typedef _Float16 v2h __attribute__((ext_vector_type(2)));
     typedef float v2f __attribute__((ext_vector_type(2)));
     auto round_pair = [](float a, float c) -> v2h { return __builtin_convertvector((v2f){a, c}, v2h); };   // to nearest
-    v4u h[NT], m[PARTS == 3 ? NT : 1], l[NT], gr;
+    v4u h[NT], m[PARTS == 3 ? NT : 1], l[NT], gr;   // gr: the rating parts (BX), the stacked parts of the last tile (STACK)
     // tile T, entry pair pr: the two fp32 values -> three packed part pairs.  ok0 / ok1: entry inside the work item
     auto cut = [&](auto ttag, int pr, float x0, float x1, const float (&r)[8], bool ok0, bool ok1, auto lasttag) {
         constexpr int T = decltype(ttag)::value;
+        if constexpr (FMA_B && WANT_B) {   // (ratings beyond the end of the work item are 0; the values there are those of row 0)
+            const float y0 = decltype(lasttag)::value ? (ok0 ? x0 : 0.f) : x0, y1 = decltype(lasttag)::value ? (ok1 ? x1 : 0.f) : x1;
+            bacc[T] = fmaf(r[2 * pr + 1], y1, fmaf(r[2 * pr], y0, bacc[T]));
+        }
         if constexpr (!BX && T == NT - 1) {   // the rating lane and the zero lanes of the last tile
             // (two parts: r / s here, so that the scaling below gives the rating back exactly; applied here and not
             // where the rating is loaded, which would make the load wait)
@@ -186,25 +174,37 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
             m[T][pr] = split16<ALS_BF16>(x0, x1);
             l[T][pr] = split16<ALS_BF16>(x0, x1);
         } else {
-            x0 *= scale;
-            x1 *= scale;
-            const v2h hh = round_pair(x0, x1);
-            h[T][pr] = __builtin_bit_cast(uint32_t, hh);
-            l[T][pr] = __builtin_bit_cast(uint32_t, round_pair(x0 - (float)hh.x, x1 - (float)hh.y));
+            // s x - h is exact in fp32 (s is a power of two): one mixed-precision fma per part and value, which rounds
+            // the product, or the difference, to fp16.  (The empty statement keeps the packed first parts in one
+            // register: the compiler would otherwise form them a second time for the difference.)
+            uint32_t hp = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, 0.f),
+                                                              (_Float16)__builtin_fmaf(x1, scale, 0.f)});
+            asm("" : "+v"(hp));
+            const v2h hh = __builtin_bit_cast(v2h, hp);
+            h[T][pr] = hp;
+            l[T][pr] = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, -(float)hh.x),
+                                                          (_Float16)__builtin_fmaf(x1, scale, -(float)hh.y)});
+        }
+        if constexpr (STACK && T == NT - 1) {
+            const uint32_t p0 = h[T][pr], p1 = PARTS == 3 ? m[PARTS == 3 ? T : 0][pr] : l[T][pr], p2 = l[T][pr];
+            gr[pr] = PARTS == 3 && part2 ? p2 : (part1 ? p1 : p0);
         }
     };
-    // reads a region back, one entry pair at a time, and cuts its tiles into parts
+    // reads the rows back, one entry pair at a time, and cuts the tiles of group G (the 16-, 8- and 4-byte parts of a
+    // lane's features) into parts
     auto read_group = [&](auto gtag, const float (&r)[8], int t, auto lasttag) {
         constexpr int G = decltype(gtag)::value;
         const int e0 = 32 * t + 8 * kq;
+        const uint32_t *const mine = fifo + 8 * F * kq;
 #pragma unroll
         for (int pr = 0; pr < 4; ++pr) {
             const bool ok0 = e0 + 2 * pr < len, ok1 = e0 + 2 * pr + 1 < len;
+            const uint32_t *const row0 = mine + (2 * pr) * F, *const row1 = mine + (2 * pr + 1) * F;
             if constexpr (G == 0 && N4 > 0) {
                 [&]<int... q>(std::integer_sequence<int, q...>) {
                     ([&] {
-                        const v4u v0 = *reinterpret_cast<const v4u *>(fifo + baseA + ((2 * pr) * N4 + q) * 256 + 4 * lane);
-                        const v4u v1 = *reinterpret_cast<const v4u *>(fifo + baseA + ((2 * pr + 1) * N4 + q) * 256 + 4 * lane);
+                        const v4u v0 = *reinterpret_cast<const v4u *>(row0 + 64 * q + 4 * i);
+                        const v4u v1 = *reinterpret_cast<const v4u *>(row1 + 64 * q + 4 * i);
                         cut(std::integral_constant<int, 4 * q>{}, pr, bits_to_float(v0[0]), bits_to_float(v1[0]), r, ok0, ok1, lasttag);
                         cut(std::integral_constant<int, 4 * q + 1>{}, pr, bits_to_float(v0[1]), bits_to_float(v1[1]), r, ok0, ok1, lasttag);
                         cut(std::integral_constant<int, 4 * q + 2>{}, pr, bits_to_float(v0[2]), bits_to_float(v1[2]), r, ok0, ok1, lasttag);
@@ -213,25 +213,20 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
                 }(std::make_integer_sequence<int, N4>{});
             }
             if constexpr (G == 1 && N2 > 0) {
-                const uint32_t a0 = fifo[baseB + ((2 * pr) * 2 + 0) * 64 + lane], a1 = fifo[baseB + ((2 * pr) * 2 + 1) * 64 + lane];
-                const uint32_t c0 = fifo[baseB + ((2 * pr + 1) * 2 + 0) * 64 + lane], c1 = fifo[baseB + ((2 * pr + 1) * 2 + 1) * 64 + lane];
-                cut(std::integral_constant<int, 4 * N4>{}, pr, bits_to_float(a0), bits_to_float(c0), r, ok0, ok1, lasttag);
-                cut(std::integral_constant<int, 4 * N4 + 1>{}, pr, bits_to_float(a1), bits_to_float(c1), r, ok0, ok1, lasttag);
+                const uint2 v0 = *reinterpret_cast<const uint2 *>(row0 + 64 * N4 + 2 * i);
+                const uint2 v1 = *reinterpret_cast<const uint2 *>(row1 + 64 * N4 + 2 * i);
+                cut(std::integral_constant<int, 4 * N4>{}, pr, bits_to_float(v0.x), bits_to_float(v1.x), r, ok0, ok1, lasttag);
+                cut(std::integral_constant<int, 4 * N4 + 1>{}, pr, bits_to_float(v0.y), bits_to_float(v1.y), r, ok0, ok1, lasttag);
             }
             if constexpr (G == 2 && N1 > 0) {
-                [&]<int... k>(std::integer_sequence<int, k...>) {
-                    ([&] {
-                        const uint32_t a0 = fifo[baseC + ((2 * pr) * N1 + k) * 64 + lane];
-                        const uint32_t c0 = fifo[baseC + ((2 * pr + 1) * N1 + k) * 64 + lane];
-                        cut(std::integral_constant<int, first1 + k>{}, pr, bits_to_float(a0), bits_to_float(c0), r, ok0, ok1, lasttag);
-                    }(), ...);
-                }(std::make_integer_sequence<int, N1>{});
+                const int ft = base1 + (STACK ? ((i & 3) < RI ? (i & 3) : RI - 1) : i);
+                cut(std::integral_constant<int, first1>{}, pr, bits_to_float(row0[ft]), bits_to_float(row1[ft]), r, ok0, ok1, lasttag);
             }
         }
     };
     auto rating_operand = [&](const float (&r)[8]) {
         gr = (v4u){0u, 0u, 0u, 0u};
-        if constexpr (BX && WANT_B) {
+        if constexpr (BX && WANT_B && !FMA_B) {
 #pragma unroll
             for (int pr = 0; pr < 4; ++pr) {
                 float r0 = r[2 * pr], r1 = r[2 * pr + 1];
@@ -258,6 +253,14 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
 #pragma unroll
                 for (int C = 0; C <= R; ++C) {
                     v4f &a = acc[tiles_below(ROWS, R) + C];
+                    if constexpr (STACK) {
+                        if (R == NT - 1) {
+                            mfma_16x16x32<PT>(a, gr, l[C]);
+                            if constexpr (PARTS == 3) mfma_16x16x32<PT>(a, gr, m[C]);
+                            mfma_16x16x32<PT>(a, gr, h[C]);
+                            continue;
+                        }
+                    }
                     mfma_16x16x32<PT>(a, h[R], l[C]);
                     mfma_16x16x32<PT>(a, l[R], h[C]);
                     if constexpr (PARTS == 3) {
@@ -267,24 +270,19 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
                     }
                     mfma_16x16x32<PT>(a, h[R], h[C]);
                 }
-                if constexpr (BX && WANT_B) {
+                if constexpr (BX && WANT_B && !FMA_B) {
                     mfma_16x16x32<PT>(bt[R], gr, l[R]);
                     if constexpr (PARTS == 3) mfma_16x16x32<PT>(bt[R], gr, m[R]);
                     mfma_16x16x32<PT>(bt[R], gr, h[R]);
                 }
             }
     };
-    constexpr int endA = 4 * N4, endB = first1;   // first tile beyond group A / groups A and B
     using T0 = std::integral_constant<int, 0>;
-    using TA = std::integral_constant<int, endA>;
-    using TB = std::integral_constant<int, endB>;
     using TN = std::integral_constant<int, NT>;
 
     float rat[8];
-    Ids ids = load_ids(0);
-    dma8_group(G0{}, ids);
-    dma8_group(G1{}, ids);
-    dma8_group(G2{}, ids);
+    int ids = load_ids(0);
+    dma_rows(ids);
     load_ratings(0, rat);
     ids = load_ids(1);   // of the next step: the loads of step t+1 go out during step t
     // one step; LAST: the final step of the work item -- entries beyond its end count as zero, nothing is prefetched
@@ -293,44 +291,59 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
         // everything this step reads from the buffer was issued a step ago
         __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         rating_operand(rat);
-        // (a region is refilled only after its values have been read AND used: the scheduling barrier keeps the
-        // loads that overwrite it behind the instructions that wait for the reads)
         read_group(G0{}, rat, t, lasttag);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!LAST) dma8_group(G0{}, ids);
-        rows_mfma(T0{}, TA{});
         read_group(G1{}, rat, t, lasttag);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!LAST) dma8_group(G1{}, ids);
-        rows_mfma(TA{}, TB{});
         read_group(G2{}, rat, t, lasttag);
+        // (the buffer is refilled only after its values have been read AND used: the scheduling barrier keeps the
+        // loads that overwrite it behind the instructions that wait for the reads)
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!LAST) {
-            dma8_group(G2{}, ids);
+            dma_rows(ids);
             load_ratings(t + 1, rat);
-            ids = load_ids(t + 2);   // (beyond the end: zeros -> row 0, read but never used)
+            ids = load_ids(t + 2);
         }
         __builtin_amdgcn_sched_barrier(0);
-        rows_mfma(TB{}, TN{});
+        rows_mfma(T0{}, TN{});
         __builtin_amdgcn_sched_barrier(0);
     };
     for (int t = 0; t + 1 < nsteps; ++t) step(std::false_type{}, t);
     step(std::true_type{}, nsteps - 1);
 
-    // b_u = row RI of the last tile row (or rows 0 .. 2 of the extra tiles), then zero the padding
+    // b_u = rows 12 .. of the stacked last tile row, or rows 0 .. 2 of the extra tiles
     const int c = i, g4 = kq;
-    if constexpr (WANT_B) {
+    if constexpr (WANT_B && FMA_B) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T) b[T] = (((ROWS >> T) & 1u) && (BX || T < NT - 1 || c < RI)) ? colsum4(bacc[T]) : 0.f;
+    } else if constexpr (WANT_B) {
+        constexpr int first_lane = STACK ? 48 : 0;   // the lane row that holds them, in registers 0 .. PARTS - 1
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
-            float s = 0.f;
-            if constexpr (BX) {
-#pragma unroll
-                for (int k = 0; k < PARTS; ++k) s += bperm(4 * c, bt[T][k]);   // rows 0..2: lane row 0, registers 0..2
-            } else {
-                s = bperm(4 * (16 * (RI / 4) + c), acc[LB + T][RI % 4]);   // row RI: lane row RI/4, register RI%4
-            }
+            float s;
+            if constexpr (STACK) s = PARTS == 3 ? acc[LB + T][0] + acc[LB + T][1] + acc[LB + T][2] : acc[LB + T][0] + acc[LB + T][1];
+            else s = PARTS == 3 ? bt[T][0] + bt[T][1] + bt[T][2] : bt[T][0] + bt[T][1];
+            s = bperm(4 * (first_lane + c), s);
             if constexpr (PARTS == 2) s *= inv_scale;   // sum of r * (s theta)
             b[T] = (((ROWS >> T) & 1u) && (BX || T < NT - 1 || c < RI)) ? s : 0.f;
+        }
+    }
+    if constexpr (STACK) {   // rows k, 4 + k and 8 + k of the last tile row add up to feature row k; the rest is padding
+        const int a16 = 4 * (lane ^ 16), a32 = 4 * (lane ^ 32);
+#pragma unroll
+        for (int T = 0; T < NT; ++T) {
+            v4f &a = acc[LB + T];
+            float t[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = g4 < PARTS ? a[r] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) t[r] = bperm(a16, a[r]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] += t[r];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) t[r] = bperm(a32, a[r]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = (g4 == 0 && r < RI && (T < NT - 1 || c < RI)) ? a[r] + t[r] : 0.f;
         }
     }
     if constexpr (PARTS == 2) {   // sums of (s theta)(s theta'): back to the caller's scale, exactly
@@ -339,15 +352,6 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
         for (int q = 0; q < tiles_in(ROWS); ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[q][r] *= inv2;
-    }
-    if constexpr (!BX) {
-#pragma unroll
-        for (int T = 0; T < NT; ++T)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool keep = (4 * g4 + r < RI) && (T < NT - 1 || c < RI);
-                acc[LB + T][r] = keep ? acc[LB + T][r] : 0.f;
-            }
     }
 }
 
