@@ -264,8 +264,10 @@ hipError_t launch_mfma_peak(int et, hipStream_t st, int workgroups, int iters, f
 hipError_t launch_copy(hipStream_t st, int workgroups, const void *src, void *dst, int64_t bytes);
 
 // transpose.hip
+// scratch: a buffer that grows on demand (hipFree + hipMalloc); waits for the stream
 hipError_t transpose_csr(bool ptr64, hipStream_t st, int64_t nrows, int64_t ncols, int64_t nnz, const void *ptr,
-                         const int32_t *idx, const float *val, void *cptr, int32_t *cidx, float *cval);
+                         const int32_t *idx, const float *val, void *cptr, int32_t *cidx, float *cval, void **scratch,
+                         size_t *scratch_bytes);
 
 inline bool supported_f(int f) { return f == 16 || f == 32 || f == 64 || f == 100 || f == 128 || f == 256; }
 // f whose lower triangle fits the registers of one wavefront (fused build+solve, wave-per-row CG)

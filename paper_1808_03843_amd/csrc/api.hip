@@ -87,6 +87,10 @@ int short_row_limit(const als_config &c) {
     return (c.factor_dtype == ALS_F32 && (c.f == 100 || c.f == 128)) ? 128 : 64;
 }
 
+// Allocating and freeing the 1.6 GB that 99M entries take costs about as much as sorting them (1.4 against 2.4 ms), and far
+// more in a tight loop, where every fresh allocation waits for the memory to be cleared
+constexpr size_t kSortKeep = (size_t)2 << 30, kSortSmall = (size_t)64 << 20;   // (up to 64 MB stay until als_destroy)
+
 struct TimedLaunch { hipEvent_t a, b; int kernel; };
 }  // namespace
 
@@ -100,6 +104,8 @@ struct als_ctx {
     size_t slots_bytes = 0;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
+    void *sort_scratch = nullptr;   // als_csr_to_csc: kept between its calls up to kSortKeep bytes, given back by the next plan build beyond kSortSmall
+    size_t sort_scratch_bytes = 0;
     int *status = nullptr;       // DEVICE status word
     int *check_flags = nullptr;  // DEVICE: result word of als_check_matrix
     unsigned long long *fp_now = nullptr;   // DEVICE: fingerprint of the row offsets of the current call (zero between calls),
@@ -161,6 +167,13 @@ void free_plan(als_ctx *ctx, Plan &p) {
     }
     delete[] p.task_off_host;
     p = Plan();
+}
+
+// (waits for the device, as hipFree does: nothing still reads the buffer)
+void free_sort_scratch(als_ctx *ctx) {
+    if (ctx->sort_scratch) (void)hipFree(ctx->sort_scratch);
+    ctx->sort_scratch = nullptr;
+    ctx->sort_scratch_bytes = 0;
 }
 
 // device memory of a plan: a piece of the arena (workspace mode; the caller has made sure the plan fits) or hipMalloc
@@ -251,6 +264,7 @@ int get_plan(als_ctx *ctx, const als_sparse *a, Plan **out) {
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         free_plan(ctx, p);
     }
+    if (ctx->sort_scratch_bytes > kSortSmall) free_sort_scratch(ctx);
     const size_t arena_mark = ctx->arena_used;
     const int rc = build_plan(ctx, a, p);
     if (rc != ALS_OK) {   // nothing of a half-built plan stays behind
@@ -700,6 +714,7 @@ void als_destroy(als_ctx *ctx) {
     (void)on_device.enter(ctx->cfg.device);
     hipStreamSynchronize(ctx->stream);
     for (auto &p : ctx->plans) free_plan(ctx, p);
+    free_sort_scratch(ctx);
     if (!ctx->fixed) {
         hipFree(ctx->slots); hipFree(ctx->scratch); hipFree(ctx->status); hipFree(ctx->sse_partial);
         hipFree(ctx->sse_total); hipFree(ctx->fp_now); hipFree(ctx->check_flags); hipFree(ctx->gram[0]); hipFree(ctx->gram[1]); hipFree(ctx->gram_dot);
@@ -955,7 +970,8 @@ static int als_csr_to_csc_impl(als_ctx *ctx, const als_sparse *csr, void *cptr_o
     DeviceGuard on_device;
     HIP_TRY(ctx, on_device.enter(ctx->cfg.device));
     hipError_t e = transpose_csr(csr->ptr_is_64 != 0, ctx->stream, csr->nrows, csr->ncols, csr->nnz, csr->ptr,
-                                 csr->idx, csr->val, cptr_out, cidx_out, cval_out);
+                                 csr->idx, csr->val, cptr_out, cidx_out, cval_out, &ctx->sort_scratch, &ctx->sort_scratch_bytes);
+    if (ctx->sort_scratch_bytes > kSortKeep || ctx->fixed || e != hipSuccess) free_sort_scratch(ctx);
     if (e != hipSuccess) return fail_hip(ctx, e, "als_csr_to_csc");
     return ALS_OK;
 }
