@@ -102,7 +102,8 @@ typedef struct als_config {
     int32_t device;       /* HIP device ordinal                                                          */
     void *stream;         /* hipStream_t to enqueue on (NULL = the default stream)                       */
     int32_t chunk;        /* stored entries per work item, a power of two in [64, 2^20]; longer rows are
-                             split (0 = default 4096)                                                    */
+                             split.  0 (default): 4096, and 512 .. 2048 for matrices of 2^18 .. 2^25 stored
+                             entries, which 4096 would leave in too few work items                       */
     int64_t batch_slots;  /* work items whose partial A_u are held at once (0 = about 4 GB worth;
                              larger values than 4,194,303 are taken as that)                                      */
     int32_t profile;      /* 1: bracket every kernel with HIP events (see als_kernel_time)               */
@@ -131,7 +132,7 @@ typedef struct als_config {
  * of m and n when both the CSR and the CSC of R are used) and max_nnz stored entries: bookkeeping, the plans of
  * two such matrices at once (more if they are smaller; when a new plan does not fit, all cached plans are
  * dropped and rebuilt on demand), one partial sum per work item, and partial Gram matrices for
- * min(batch_slots, 2 * max_nnz / chunk + 1) work items.  The workspace, workspace_bytes and workspace_max_* fields
+ * min(batch_slots, 2 * max_nnz / chunk + 1) work items (chunk = 0: the most that any matrix within the maxima has).  The workspace, workspace_bytes and workspace_max_* fields
  * of cfg are ignored.  Returns 0 for a configuration als_create would refuse.  Needs no device. */
 size_t als_workspace_bytes(const als_config *cfg, int64_t max_rows, int64_t max_nnz);
 

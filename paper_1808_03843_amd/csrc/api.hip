@@ -28,15 +28,43 @@ constexpr int kMaxPlans = 4;
 // ---- layout of a caller's workspace ---------------------------------------------------------------------------
 constexpr size_t kAlign = 256;
 constexpr size_t aligned(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
-// upper bounds that hold for every matrix with `rows` rows and `nnz` stored entries: a row of n_u entries has
+// Stored entries per work item when the configuration leaves the choice to the library (chunk = 0), by the entries of
+// the matrix.  One wavefront takes an item from end to end (about 45 ns an entry at f = 100), so a small matrix in long
+// items leaves most of the chip waiting for a few wavefronts; short items cost a partial Gram matrix each (29 KB written
+// and read at f = 100) and more rows that cannot be built and solved in one go.  Measured at 4096 / 2048 / 1024 / 512 /
+// 256 entries, ms per sweep: 1.5M entries, f = 100, CG 0.63 / 0.58 / 0.44 / 0.41 / 0.45; 0.6M, f = 100, exact 1.11 / 0.78 /
+// 0.61 / 0.54 / 0.53; 25M, f = 100, exact 5.14 / 5.02 / 5.27 / 5.99, implicit 6.21 / 6.00 / 6.00 / 6.45; 60k, f = 16,
+// exact 0.076 / 0.076 / 0.116 / 0.136 (few rows that long: the launches of the split rows are not worth it).
+constexpr int kDefaultChunk = 4096;
+struct ChunkBySize { int64_t below; int chunk; };
+constexpr ChunkBySize kChunkBySize[] = {
+    {1ll << 18, kDefaultChunk}, {1ll << 21, 512}, {1ll << 23, 1024}, {1ll << 25, 2048}, {INT64_MAX, kDefaultChunk}};
+int chunk_of(const als_config &c, int64_t nnz) {
+    if (c.chunk != 0) return c.chunk;
+    for (const auto &r : kChunkBySize)
+        if (nnz < r.below) return r.chunk;
+    return kDefaultChunk;
+}
+// the largest times * entries / chunk_of(entries) of any matrix with at most nnz entries
+int64_t max_items(const als_config &c, int64_t nnz, int64_t times) {
+    if (c.chunk != 0) return times * nnz / c.chunk;
+    int64_t most = 0;
+    for (const auto &r : kChunkBySize) {
+        const int64_t items = times * (nnz < r.below ? nnz : r.below - 1) / r.chunk;
+        if (items > most) most = items;
+        if (nnz < r.below) break;
+    }
+    return most;
+}
+// upper bounds that hold for every matrix with at most `rows` rows and `nnz` stored entries: a row of n_u entries has
 // ceil(n_u / chunk) work items, and only rows with n_u >= chunk (fewer than 2 n_u / chunk items each) use slots
-int64_t max_tasks(int64_t rows, int64_t nnz, int chunk) { return rows + nnz / chunk; }
-int64_t max_slot_tasks(int64_t rows, int64_t nnz, int chunk) {
-    const int64_t a = max_tasks(rows, nnz, chunk), b = 2 * nnz / chunk;
+int64_t max_tasks(const als_config &c, int64_t rows, int64_t nnz) { return rows + max_items(c, nnz, 1); }
+int64_t max_slot_tasks(const als_config &c, int64_t rows, int64_t nnz) {
+    const int64_t a = max_tasks(c, rows, nnz), b = max_items(c, nnz, 2);
     return a < b ? a : b;
 }
-size_t plan_bytes_bound(int64_t rows, int64_t nnz, int chunk) {
-    const size_t t = (size_t)max_tasks(rows, nnz, chunk), s = (size_t)max_slot_tasks(rows, nnz, chunk);
+size_t plan_bytes_bound(const als_config &c, int64_t rows, int64_t nnz) {
+    const size_t t = (size_t)max_tasks(c, rows, nnz), s = (size_t)max_slot_tasks(c, rows, nnz);
     return aligned(4 * (size_t)(rows > 0 ? rows : 1)) + aligned(4 * (size_t)(rows + 1)) + 2 * aligned(4 * (t > 0 ? t : 1)) +
            aligned(4 * (s > 0 ? s : 1)) + aligned(16);
 }
@@ -47,24 +75,24 @@ struct WorkspaceLayout {   // byte offsets of the pieces; `total` is what als_wo
     size_t fixed_words, gram0, gram1, sse_partial, scratch, scratch_bytes, slots, arena, arena_bytes, total;
     int64_t slot_capacity;
 };
-// cfg: chunk and batch_slots already resolved (no zeros)
+// cfg: batch_slots already resolved (not zero)
 WorkspaceLayout workspace_layout(const als_config &c, int64_t rows, int64_t nnz) {
     WorkspaceLayout L{};
     size_t o = 0;
     L.fixed_words = o; o += aligned(1024);   // status, check flags, fingerprint + counter, sums, class starts
     L.gram0 = o; o += aligned(sizeof(float) * (size_t)slot_floats(c.f));
     L.gram1 = o; o += aligned(sizeof(float) * (size_t)slot_floats(c.f));
-    L.sse_partial = o; o += aligned(sizeof(double) * (size_t)(max_tasks(rows, nnz, c.chunk) + 1));
+    L.sse_partial = o; o += aligned(sizeof(double) * (size_t)(max_tasks(c, rows, nnz) + 1));
     // plan scratch; also holds the sort keys of the slot work items (one int each)
     L.scratch_bytes = plan_scratch_bytes(rows, kPlanClasses);
-    const size_t keys = 4 * (size_t)(max_slot_tasks(rows, nnz, c.chunk) + 1);
+    const size_t keys = 4 * (size_t)(max_slot_tasks(c, rows, nnz) + 1);
     if (keys > L.scratch_bytes) L.scratch_bytes = keys;
     L.scratch_bytes = aligned(L.scratch_bytes);
     L.scratch = o; o += L.scratch_bytes;
-    L.slot_capacity = max_slot_tasks(rows, nnz, c.chunk) + 1;
+    L.slot_capacity = max_slot_tasks(c, rows, nnz) + 1;
     if (L.slot_capacity > c.batch_slots) L.slot_capacity = c.batch_slots;
     L.slots = o; o += aligned((size_t)L.slot_capacity * slot_bytes(c));
-    L.arena_bytes = 2 * plan_bytes_bound(rows, nnz, c.chunk);
+    L.arena_bytes = 2 * plan_bytes_bound(c, rows, nnz);
     L.arena = o; o += L.arena_bytes;
     L.total = o;
     return L;
@@ -243,7 +271,7 @@ int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p);
 // Finds or builds the plan of a matrix: degree-class permutation, work items, launch order of the slot work items.
 int get_plan(als_ctx *ctx, const als_sparse *a, Plan **out) {
     for (auto &p : ctx->plans)
-        if (p.key_ptr == a->ptr && p.nrows == a->nrows && p.nnz == a->nnz && p.chunk == ctx->cfg.chunk) {
+        if (p.key_ptr == a->ptr && p.nrows == a->nrows && p.nnz == a->nnz) {
             *out = &p;
             return ALS_OK;
         }
@@ -252,7 +280,7 @@ int get_plan(als_ctx *ctx, const als_sparse *a, Plan **out) {
         // the arena holds two plans of the largest matrix the workspace was sized for.  Kernels of earlier calls
         // that still read the old plans are ahead of the new plan's kernels on the stream.
         const bool table_full = ctx->plans[kMaxPlans - 1].key_ptr != nullptr;
-        if (table_full || ctx->arena_used + plan_bytes_bound(a->nrows, a->nnz, ctx->cfg.chunk) > ctx->arena_bytes) {
+        if (table_full || ctx->arena_used + plan_bytes_bound(ctx->cfg, a->nrows, a->nnz) > ctx->arena_bytes) {
             for (auto &p : ctx->plans) free_plan(ctx, p);
             ctx->arena_used = 0;
             ctx->next_plan = 0;
@@ -320,6 +348,7 @@ int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p) {
     Timed timed(ctx, ALS_K_PLAN);
     const int64_t m = a->nrows;
     const bool p64 = a->ptr_is_64 != 0;
+    p.chunk = chunk_of(ctx->cfg, a->nnz);
     HIP_TRY(ctx, plan_alloc(ctx, &p.perm, sizeof(int32_t) * (size_t)(m > 0 ? m : 1)));
     HIP_TRY(ctx, plan_alloc(ctx, &p.task_off, sizeof(int32_t) * (size_t)(m + 1)));
     int32_t *class_start_dev = ctx->class_start_dev;
@@ -334,12 +363,12 @@ int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p) {
     HIP_TRY(ctx, eb);
     {   // rows with >= chunk = 2^j entries are the classes >= j+1, i.e. the first class_start[...] positions
         int j = 0;
-        while ((1 << j) < ctx->cfg.chunk) ++j;
+        while ((1 << j) < p.chunk) ++j;
         p.split_pos = class_start[kPlanClasses - 1 - j];
     }
     for (int c = 0; c <= 32; ++c)   // class c = 1 + floor(log2 n_u) (0 for empty rows), heaviest class first in perm
         p.rows_ge[c] = c == 0 ? m : (c < kPlanClasses ? class_start[kPlanClasses - c] : 0);
-    HIP_TRY(ctx, plan_tasks(p64, ctx->stream, m, a->ptr, p.perm, ctx->cfg.chunk, p.task_off, &ctx->scratch,
+    HIP_TRY(ctx, plan_tasks(p64, ctx->stream, m, a->ptr, p.perm, p.chunk, p.task_off, &ctx->scratch,
                             &ctx->scratch_bytes, ctx->fixed));
     p.task_off_host = new (std::nothrow) int32_t[(size_t)m + 1];
     if (!p.task_off_host) return fail(ctx, ALS_ENOMEM, "host allocation of the work-item offsets failed");
@@ -349,8 +378,7 @@ int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p) {
     p.ntasks = p.task_off_host[m];
     HIP_TRY(ctx, plan_alloc(ctx, &p.task_row, sizeof(int32_t) * (size_t)(p.ntasks > 0 ? p.ntasks : 1)));
     HIP_TRY(ctx, plan_alloc(ctx, &p.task_chunk, sizeof(int32_t) * (size_t)(p.ntasks > 0 ? p.ntasks : 1)));
-    HIP_TRY(ctx, plan_emit(p64, ctx->stream, m, a->ptr, p.perm, ctx->cfg.chunk, p.task_off, p.task_row, p.task_chunk));
-    p.chunk = ctx->cfg.chunk;
+    HIP_TRY(ctx, plan_emit(p64, ctx->stream, m, a->ptr, p.perm, p.chunk, p.task_off, p.task_row, p.task_chunk));
     const int rc = build_order(ctx, a, p);
     if (rc != ALS_OK) return rc;
     HIP_TRY(ctx, plan_alloc(ctx, &p.fingerprint, 2 * sizeof(unsigned long long)));
@@ -494,14 +522,14 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
             Timed t(ctx, ALS_K_HERMITIAN);
             if (implicit)
                 HIP_TRY(ctx, launch_hermitian_implicit(f, p64, wide, ctx->cfg.factor_dtype, ctx->stream, p->task_row, p->task_chunk, order, task0,
-                                                       ntasks, ctx->cfg.chunk, a->ptr, a->idx, a->val, G, alpha,
+                                                       ntasks, p->chunk, a->ptr, a->idx, a->val, G, alpha,
                                                        ctx->slots));
             else if (x2)
                 HIP_TRY(ctx, launch_hermitian_x2(f, p64, wide, s16, ctx->stream, p->task_row, p->task_chunk, order, task0,
-                                                 ntasks, ctx->cfg.chunk, a->ptr, a->idx, a->val, G, ctx->slots, ctx->absmax));
+                                                 ntasks, p->chunk, a->ptr, a->idx, a->val, G, ctx->slots, ctx->absmax));
             else
                 HIP_TRY(ctx, launch_hermitian(f, p64, wide, ctx->cfg.factor_dtype, s16, ctx->stream, p->task_row,
-                                              p->task_chunk, order, task0, ntasks, ctx->cfg.chunk, a->ptr, a->idx, a->val, G,
+                                              p->task_chunk, order, task0, ntasks, p->chunk, a->ptr, a->idx, a->val, G,
                                               ctx->slots));
         }
         {
@@ -609,7 +637,7 @@ int guarded(als_ctx *ctx, L body) {
 
 extern "C" {
 
-// Checks a configuration and fills in its defaults (chunk, batch_slots).  false: als_create refuses it.
+// Checks a configuration and fills in its defaults (batch_slots; chunk = 0 stays: see chunk_of).  false: als_create refuses it.
 static bool resolve_config(const als_config *in, als_config *c) {
     *c = *in;
     if (!supported_f(c->f)) return false;
@@ -629,7 +657,6 @@ static bool resolve_config(const als_config *in, als_config *c) {
         return false;
     if (c->chunk < 0 || c->batch_slots < 0) return false;
     if (c->chunk != 0 && (c->chunk < 64 || c->chunk > (1 << 20) || (c->chunk & (c->chunk - 1)))) return false;
-    if (c->chunk == 0) c->chunk = 4096;
     if (c->batch_slots > max_workgroups(kWideThreads)) c->batch_slots = max_workgroups(kWideThreads);
     if (c->batch_slots == 0) {   // about 4 GB of slots
         c->batch_slots = 131072;
@@ -855,7 +882,7 @@ static int sum_over_entries(als_ctx *ctx, const als_sparse *csr, const float *X,
     {
         Timed t(ctx, ALS_K_RMSE);
         HIP_TRY(ctx, launch_sse(f, csr->ptr_is_64 != 0, implicit, alpha, ctx->stream, p->task_row, p->task_chunk,
-                                p->ntasks, ctx->cfg.chunk, csr->ptr, csr->idx, csr->val, X, Theta, ctx->sse_partial,
+                                p->ntasks, p->chunk, csr->ptr, csr->idx, csr->val, X, Theta, ctx->sse_partial,
                                 ctx->sse_total));
     }
     double sse = 0.0;
@@ -879,6 +906,7 @@ static int als_hermitian_impl(als_ctx *ctx, const als_sparse *csr, const void *T
     HIP_TRY(ctx, on_device.enter(ctx->cfg.device));
     // a throw-away plan over the row range, in natural order
     const bool p64 = csr->ptr_is_64 != 0;
+    const int chunk = ctx->cfg.chunk != 0 ? ctx->cfg.chunk : kDefaultChunk;
     const size_t esize = factor_bytes(ctx->cfg.factor_dtype);
     const bool wide = needs_wide_offsets(csr->ncols, f, esize);
     int32_t *perm = nullptr, *task_off = nullptr, *task_row = nullptr, *task_chunk = nullptr;
@@ -894,7 +922,7 @@ static int als_hermitian_impl(als_ctx *ctx, const als_sparse *csr, const void *T
     size_t tmp_bytes = 0;
     auto cleanup_tmp = [&]() { hipFree(tmp); tmp = nullptr; };
     if ((e = fill_iota(ctx->stream, perm, nrows, (int32_t)row0)) != hipSuccess ||
-        (e = plan_tasks(p64, ctx->stream, nrows, csr->ptr, perm, ctx->cfg.chunk, task_off, &tmp, &tmp_bytes, false)) !=
+        (e = plan_tasks(p64, ctx->stream, nrows, csr->ptr, perm, chunk, task_off, &tmp, &tmp_bytes, false)) !=
             hipSuccess ||
         (e = hipMemcpyAsync(off.data(), task_off, sizeof(int32_t) * (size_t)(nrows + 1), hipMemcpyDeviceToHost,
                             ctx->stream)) != hipSuccess ||
@@ -907,7 +935,7 @@ static int als_hermitian_impl(als_ctx *ctx, const als_sparse *csr, const void *T
     const int64_t ntasks = off[(size_t)nrows];
     if ((e = hipMalloc(&task_row, sizeof(int32_t) * (size_t)(ntasks > 0 ? ntasks : 1))) != hipSuccess ||
         (e = hipMalloc(&task_chunk, sizeof(int32_t) * (size_t)(ntasks > 0 ? ntasks : 1))) != hipSuccess ||
-        (e = plan_emit(p64, ctx->stream, nrows, csr->ptr, perm, ctx->cfg.chunk, task_off, task_row, task_chunk)) !=
+        (e = plan_emit(p64, ctx->stream, nrows, csr->ptr, perm, chunk, task_off, task_row, task_chunk)) !=
             hipSuccess) {
         cleanup();
         return fail_hip(ctx, e, "work items of the row range");
@@ -920,10 +948,10 @@ static int als_hermitian_impl(als_ctx *ctx, const als_sparse *csr, const void *T
             e = launch_absmax(ctx->stream, static_cast<const float *>(Theta), csr->ncols * (int64_t)f, ctx->absmax);
             if (e == hipSuccess)
                 e = launch_hermitian_x2(f, p64, wide, false, ctx->stream, task_row, task_chunk, nullptr, 0, ntasks,
-                                        ctx->cfg.chunk, csr->ptr, csr->idx, csr->val, Theta, ctx->slots, ctx->absmax);
+                                        chunk, csr->ptr, csr->idx, csr->val, Theta, ctx->slots, ctx->absmax);
         } else {
             e = launch_hermitian(f, p64, wide, ctx->cfg.factor_dtype, false, ctx->stream, task_row, task_chunk, nullptr, 0,
-                                 ntasks, ctx->cfg.chunk, csr->ptr, csr->idx, csr->val, Theta, ctx->slots);
+                                 ntasks, chunk, csr->ptr, csr->idx, csr->val, Theta, ctx->slots);
         }
     }
     if (e == hipSuccess)
