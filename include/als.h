@@ -83,11 +83,17 @@ typedef struct als_config {
                              with ALS_F16 to 2^-24 of max(|r_uv|, 1), the spacing of the smallest fp16 numbers
                              being 2^-24 (ratings and counts of 1 and more, as in Sections 5.1 and 5.6, lose
                              nothing; a rating of 0.02 carries a relative error of up to 3e-6 into b_u).
+                             ALS_F32: with explicit feedback and a matrix of 2^18 and more entries, rows of 64 and more
+                             entries are multiplied on the 16-bit matrix cores as two fp16 parts per value (see ALS_F32X2),
+                             where a scan of the gathered matrix finds that this costs no accuracy: the largest value of
+                             every row and of every feature is 0 or at least 2^-14 of the largest of all, all are finite
+                             and that one is at least 2^-46.  Otherwise, and for work items of more than 4096 entries, on the fp32
+                             matrix instructions.  b_u is summed in fp32 either way.
                              ALS_F32X3: the gathered matrix is fp32 as with ALS_F32, but get_hermitian and get_bias
                              run on the 16-bit matrix cores: every value is cut into three bf16 parts that add up
                              to it exactly, and a product is the sum of the six part products that matter (what is
                              dropped is below 2^-23 of the product, one fp32 rounding).  Same tolerances as
-                             ALS_F32, about 1.25 times its speed (Mid shape); f <= 128, explicit feedback only.
+                             ALS_F32; f <= 128, explicit feedback only.
                              ALS_F32X2: likewise fp32 in memory, but two fp16 parts per value, h = fp16(s x) and
                              l = fp16(s x - h), rounded to nearest (|s x - h - l| <= 2^-22 |s x|), and the three
                              products h h' + h l' + l h'.  s is a power of two chosen per call from max |x| of the

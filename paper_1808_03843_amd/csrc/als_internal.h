@@ -65,6 +65,10 @@ constexpr int kWave = 64;
 // what the gathered accumulation computes (template parameter MODE of the kernels)
 constexpr int kExplicit = 0;   // eq. (2): sum theta theta^T, b = sum r theta
 constexpr int kImplicit = 1;   // Section 5.6: sum alpha*r theta theta^T, b = sum (1 + alpha*r) theta over r > 0
+// element type of the kernels for ALS_F32 factors that choose between two fp16 parts and fp32 MFMAs (hermitian_auto.hip)
+constexpr int kF32Auto = 16;
+// words of the range of a factor (k_factor_range); kRangeWork: count of finished workgroups, max, smallest row maximum
+constexpr int kRangeMax = 0, kRangeWide = 1, kRangeWork = 2, kRangeFeatures = 8, kRangeWords = 8 + 256;
 constexpr int kGram = 2;       // rows s0..s0+len of the factor matrix itself, unit weights, no b
 
 struct Plan {                     // per sparse matrix, built once and cached
@@ -119,6 +123,20 @@ hipError_t launch_hermitian_cg_x2(int f, bool ptr64, bool wide, int solver, hipS
                                   const void *Theta, float lambda, int fs, float eps, float *Xout, int *status,
                                   const uint32_t *absmax);
 
+// factor_dtype = ALS_F32, f <= 128, explicit feedback (hermitian_auto.hip): two fp16 parts where the range of the factor
+// allows it, fp32 MFMAs otherwise.  range: DEVICE, kRangeWords words, zeroed once; launch_factor_range on the same
+// stream before these.  Work items of at most kTwoPartMaxItem entries, rows of class kTwoPartMinRowClass and above.
+constexpr int kTwoPartMaxItem = 4096, kTwoPartMinRowClass = 7;   // class 7: at least 64 entries
+hipError_t launch_factor_range(int f, hipStream_t st, const float *G, int64_t n, uint32_t *range);
+hipError_t launch_hermitian_auto(int f, bool ptr64, bool wide, bool s16, hipStream_t st, const int32_t *task_row,
+                                 const int32_t *task_chunk, const int32_t *task_order, int64_t task0, int64_t ntasks,
+                                 int chunk, const void *ptr, const int32_t *idx, const float *val, const void *Theta,
+                                 float *slots, const uint32_t *range);
+hipError_t launch_hermitian_cg_auto(int f, bool ptr64, bool wide, int solver, hipStream_t st, const int32_t *perm,
+                                    int64_t pos0, int64_t npos, const void *ptr, const int32_t *idx, const float *val,
+                                    const void *Theta, float lambda, int fs, float eps, float *Xout, int *status,
+                                    const uint32_t *range);
+
 // cg_short.hip: Algorithm 1 on the gathered rows themselves (A_u p = G^T (G p) + lambda n_u p), one wavefront per
 // row, or 2 or 4 rows per wavefront, for the rows perm[pos0 .. pos0+npos) which must have fewer than
 // 64 / rows_per_wave entries (f = 256: rows_per_wave = 1, two wavefronts per row); rows_per_wave = -2 (f <= 128): two
@@ -138,10 +156,22 @@ hipError_t launch_solve_cg_wave(int f, bool ptr64, bool s16, int solver, hipStre
 // launchers above; Algorithm 1 only (the exact solver at this width is in wide_ldlt.hip, declared below).
 hipError_t launch_hermitian_wide(bool ptr64, bool wide, int et, bool s16, hipStream_t st, const int32_t *task_row,
                                  const int32_t *task_chunk, const int32_t *task_order, int64_t task0, int64_t ntasks, int chunk, const void *ptr,
-                                 const int32_t *idx, const float *val, const void *Theta, float *slots);
+                                 const int32_t *idx, const float *val, const void *Theta, float *slots,
+                                 const uint32_t *range = nullptr);
 hipError_t launch_hermitian_cg_wide(int f, bool ptr64, bool wide, int et, hipStream_t st, const int32_t *perm, int64_t pos0,
                                     int64_t npos, const void *ptr, const int32_t *idx, const float *val,
-                                    const void *Theta, float lambda, int fs, float eps, float *Xout, int *status);
+                                    const void *Theta, float lambda, int fs, float eps, float *Xout, int *status,
+                                    const uint32_t *range = nullptr);
+// factor_dtype = ALS_F32 (wide_auto.hip): two fp16 parts, launched beside the fp32 kernels above with the same range
+// (launch_factor_range): of the two the verdict lets one run
+hipError_t launch_hermitian_wide_auto(bool ptr64, bool wide, bool s16, hipStream_t st, const int32_t *task_row,
+                                      const int32_t *task_chunk, const int32_t *task_order, int64_t task0, int64_t ntasks,
+                                      int chunk, const void *ptr, const int32_t *idx, const float *val, const void *Theta,
+                                      float *slots, const uint32_t *range);
+hipError_t launch_hermitian_cg_wide_auto(bool ptr64, bool wide, hipStream_t st, const int32_t *perm, int64_t pos0,
+                                         int64_t npos, const void *ptr, const int32_t *idx, const float *val,
+                                         const void *Theta, float lambda, int fs, float eps, float *Xout, int *status,
+                                         const uint32_t *range);
 // exact solver at f = 256 (wide_ldlt.hip): fused with the build for short rows, from fp32 slots otherwise
 hipError_t launch_hermitian_ldlt_wide(bool ptr64, bool wide, int et, hipStream_t st, const int32_t *perm, int64_t pos0,
                                       int64_t npos, const void *ptr, const int32_t *idx, const float *val,

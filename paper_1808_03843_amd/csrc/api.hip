@@ -71,6 +71,8 @@ size_t plan_bytes_bound(const als_config &c, int64_t rows, int64_t nnz) {
 size_t slot_bytes(const als_config &c) {
     return sizeof(float) * (size_t)(c.herm_dtype == ALS_BF16 ? slot_words16(c.f) : slot_floats(c.f));
 }
+constexpr size_t kRangeAt = 512, kFixedBytes = 1792;   // of the fixed words of a workspace
+static_assert(kRangeAt + 4 * kRangeWords <= kFixedBytes);
 struct WorkspaceLayout {   // byte offsets of the pieces; `total` is what als_workspace_bytes returns
     size_t fixed_words, gram0, gram1, sse_partial, scratch, scratch_bytes, slots, arena, arena_bytes, total;
     int64_t slot_capacity;
@@ -79,7 +81,7 @@ struct WorkspaceLayout {   // byte offsets of the pieces; `total` is what als_wo
 WorkspaceLayout workspace_layout(const als_config &c, int64_t rows, int64_t nnz) {
     WorkspaceLayout L{};
     size_t o = 0;
-    L.fixed_words = o; o += aligned(1024);   // status, check flags, fingerprint + counter, sums, class starts
+    L.fixed_words = o; o += aligned(kFixedBytes);   // status, check flags, fingerprint + counter, sums, class starts, range
     L.gram0 = o; o += aligned(sizeof(float) * (size_t)slot_floats(c.f));
     L.gram1 = o; o += aligned(sizeof(float) * (size_t)slot_floats(c.f));
     L.sse_partial = o; o += aligned(sizeof(double) * (size_t)(max_tasks(c, rows, nnz) + 1));
@@ -115,6 +117,14 @@ int short_row_limit(const als_config &c) {
     return (c.factor_dtype == ALS_F32 && (c.f == 100 || c.f == 128)) ? 128 : 64;
 }
 
+// fp32 factors: whether a half-sweep scans its gathered factor and takes two fp16 parts per value where its range allows
+// (hermitian_auto.hip).  Small matrices are left on the fp32 matrix instructions: the scan and the longer start of the
+// other loop gain nothing there (60,000 entries, f = 16: 45 us a sweep, 5 us of it for one more launch)
+constexpr int64_t kTwoPartMinEntries = 1 << 18;
+bool two_part_route(const als_config &c, const als_sparse *a) {
+    return c.factor_dtype == ALS_F32 && chunk_of(c, a->nnz) <= kTwoPartMaxItem && a->nnz >= kTwoPartMinEntries;
+}
+
 // Allocating and freeing the 1.6 GB that 99M entries take costs about as much as sorting them (1.4 against 2.4 ms), and far
 // more in a tight loop, where every fresh allocation waits for the memory to be cleared
 constexpr size_t kSortKeep = (size_t)2 << 30, kSortSmall = (size_t)64 << 20;   // (up to 64 MB stay until als_destroy)
@@ -140,6 +150,7 @@ struct als_ctx {
                                             // followed by the 32-bit count of finished workgroups (fp_done)
     unsigned int *fp_done = nullptr;
     uint32_t *absmax = nullptr;  // DEVICE: bits of max |gathered factor| of the current update (factor_dtype ALS_F32X2)
+    uint32_t *range = nullptr;   // DEVICE, kRangeWords words: range of the gathered factor of the current update (ALS_F32)
     double *sse_partial = nullptr;
     size_t sse_partial_bytes = 0;
     double *sse_total = nullptr; // DEVICE
@@ -511,6 +522,8 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
     const bool x2 = ctx->cfg.factor_dtype == ALS_F32X2;
     if (x2 && !implicit)   // the power-of-two scale of the two-part route follows max |G|
         HIP_TRY(ctx, launch_absmax(ctx->stream, static_cast<const float *>(G), a->ncols * (int64_t)f, ctx->absmax));
+    const bool two_part = !implicit && two_part_route(ctx->cfg, a);
+    if (two_part) HIP_TRY(ctx, launch_factor_range(f, ctx->stream, static_cast<const float *>(G), a->ncols, ctx->range));
     int64_t pos = 0;
     while (pos < slot_rows) {
         // rows [pos, end): as many as fit in `cap` slots, at least one row
@@ -527,6 +540,9 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
             else if (x2)
                 HIP_TRY(ctx, launch_hermitian_x2(f, p64, wide, s16, ctx->stream, p->task_row, p->task_chunk, order, task0,
                                                  ntasks, p->chunk, a->ptr, a->idx, a->val, G, ctx->slots, ctx->absmax));
+            else if (two_part)
+                HIP_TRY(ctx, launch_hermitian_auto(f, p64, wide, s16, ctx->stream, p->task_row, p->task_chunk, order, task0,
+                                                   ntasks, p->chunk, a->ptr, a->idx, a->val, G, ctx->slots, ctx->range));
             else
                 HIP_TRY(ctx, launch_hermitian(f, p64, wide, ctx->cfg.factor_dtype, s16, ctx->stream, p->task_row,
                                               p->task_chunk, order, task0, ntasks, p->chunk, a->ptr, a->idx, a->val, G,
@@ -556,7 +572,7 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
     }
     // Exact solver: rows with fewer entries than features are solved in the dual form, an
     // n_u x n_u system (dual.hip).  They are the tail of perm: fewer than 2^(c-1) entries from rows_ge[c] on.
-    int64_t fused_end = m;
+    int64_t fused_begin = slot_rows, fused_end = m;
     const int64_t piece = max_workgroups(one_wave ? 64 : kWideThreads);
     if (kDualExact && !implicit && !cg) {
         Timed t(ctx, ALS_K_FUSED);
@@ -597,9 +613,23 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
             }
         }
     }
-    if (slot_rows < fused_end) {
+    if (two_part && (one_wave || cg) && slot_rows < fused_end) {   // rows of 64 and more entries; the rest follows below
+        const int64_t hi = p->rows_ge[kTwoPartMinRowClass] < fused_end ? p->rows_ge[kTwoPartMinRowClass] : fused_end;
+        if (slot_rows < hi) {
+            Timed t(ctx, ALS_K_FUSED);
+            rc = in_pieces(slot_rows, hi - slot_rows, piece, [&](int64_t pos0, int64_t npos) {
+                HIP_TRY(ctx, launch_hermitian_cg_auto(f, p64, wide, ctx->cfg.solver, ctx->stream, p->perm, pos0, npos, a->ptr,
+                                                      a->idx, a->val, G, lambda, ctx->cfg.cg_iters, ctx->cfg.cg_eps, Out,
+                                                      ctx->status, ctx->range));
+                return (int)ALS_OK;
+            });
+            if (rc != ALS_OK) return rc;
+            fused_begin = hi;
+        }
+    }
+    if (fused_begin < fused_end) {
         Timed t(ctx, ALS_K_FUSED);
-        rc = in_pieces(slot_rows, fused_end - slot_rows, piece, [&](int64_t pos0, int64_t npos) {
+        rc = in_pieces(fused_begin, fused_end - fused_begin, piece, [&](int64_t pos0, int64_t npos) {
             if (implicit)
                 HIP_TRY(ctx, launch_hermitian_cg_implicit(f, p64, wide, ctx->cfg.factor_dtype, ctx->cfg.solver, ctx->stream, p->perm,
                                                           pos0, npos, a->ptr, a->idx, a->val, G, lambda, alpha, gram,
@@ -697,7 +727,7 @@ int als_create(als_ctx **out, const als_config *cfg) {
     bool ok = on_device.enter(c.device) == hipSuccess;
     if (ok && fixed) {
         char *w = static_cast<char *>(c.workspace);
-        char *fw = w + L.fixed_words;                       // 1 KiB of small words, 16 bytes apart at least
+        char *fw = w + L.fixed_words;                       // small words, 16 bytes apart at least
         ctx->status = reinterpret_cast<int *>(fw);
         ctx->check_flags = reinterpret_cast<int *>(fw + 16);
         ctx->fp_now = reinterpret_cast<unsigned long long *>(fw + 32);   // fingerprint, then the counter
@@ -705,6 +735,7 @@ int als_create(als_ctx **out, const als_config *cfg) {
         ctx->gram_dot = reinterpret_cast<double *>(fw + 96);             // 3 doubles
         ctx->absmax = reinterpret_cast<uint32_t *>(fw + 128);
         ctx->class_start_dev = reinterpret_cast<int32_t *>(fw + 256);    // kPlanClasses + 1 ints
+        ctx->range = reinterpret_cast<uint32_t *>(fw + kRangeAt);
         ctx->gram[0] = reinterpret_cast<float *>(w + L.gram0);
         ctx->gram[1] = reinterpret_cast<float *>(w + L.gram1);
         ctx->sse_partial = reinterpret_cast<double *>(w + L.sse_partial);
@@ -716,12 +747,12 @@ int als_create(als_ctx **out, const als_config *cfg) {
         ctx->slot_capacity = L.slot_capacity;
         ctx->arena = w + L.arena;
         ctx->arena_bytes = L.arena_bytes;
-        ok = fill_zero(ctx->stream, fw, 256) == hipSuccess;   // status, flags, fingerprint and counter start at zero
+        ok = fill_zero(ctx->stream, fw, kFixedBytes / 4) == hipSuccess;   // status, flags, fingerprint and counter start at zero
     } else if (ok) {
         ok = hipMalloc(&ctx->status, sizeof(int)) == hipSuccess && hipMalloc(&ctx->sse_total, sizeof(double)) == hipSuccess &&
-             hipMalloc(&ctx->fp_now, 3 * sizeof(unsigned long long)) == hipSuccess &&   // + the word of absmax
+             hipMalloc(&ctx->fp_now, 4 * sizeof(unsigned long long) + 4 * kRangeWords) == hipSuccess &&   // + absmax, range
              hipMemsetAsync(ctx->status, 0, sizeof(int), ctx->stream) == hipSuccess &&
-             hipMemsetAsync(ctx->fp_now, 0, 2 * sizeof(unsigned long long), ctx->stream) == hipSuccess;
+             hipMemsetAsync(ctx->fp_now, 0, 4 * sizeof(unsigned long long) + 4 * kRangeWords, ctx->stream) == hipSuccess;
     }
     if (ok) ok = gram_static_scratch(&ctx->gram_static) == hipSuccess;   // the context's device is current here
     if (!ok) {
@@ -730,7 +761,10 @@ int als_create(als_ctx **out, const als_config *cfg) {
         return ALS_EHIP;
     }
     ctx->fp_done = reinterpret_cast<unsigned int *>(ctx->fp_now + 1);
-    if (!fixed) ctx->absmax = reinterpret_cast<uint32_t *>(ctx->fp_now + 2);
+    if (!fixed) {
+        ctx->absmax = reinterpret_cast<uint32_t *>(ctx->fp_now + 2);
+        ctx->range = reinterpret_cast<uint32_t *>(ctx->fp_now + 4);
+    }
     *out = ctx;
     return ALS_OK;
 }

@@ -1,0 +1,219 @@
+// factor_dtype = ALS_F32, explicit feedback: get_hermitian on the 16-bit matrix cores where two fp16 parts
+// per value (tiles_x3.h, PARTS = 2) lose nothing against fp32 matrix instructions, and on the fp32 ones otherwise.
+// A scan of the gathered factor before the kernels of a half-sweep decides which (k_factor_range); every wavefront
+// reads the verdict and takes one of the two loops.  The kernels are the templates of hermitian_kernels.h.
+//
+// Why: fp32 MFMAs run at 1/16 of the rate of the 16-bit ones and share the issue port with the vector ALU, so the fp32
+// loop is bound by them (k_hermitian 112 of 141 TFLOP/s).  Two parts take 3 (77 MFMAs a step of 32 entries at
+// f = 100) where fp32 takes 8 x 28: Mid shape, CG(6), ms per sweep
+// f = 16 3.45 -> 2.18, 32 4.34 -> 2.67, 64 9.06 -> 5.40, 100 18.9 -> 11.5, 128 28.1 -> 17.0; 120,047 x 17,771 with 25M entries, exact,
+// f = 100 7.3 -> 5.0; the scan included.
+//
+// Accuracy.  A value s x = h + l + d has |d| <= 2^-22 |s x| (rounded to nearest twice: 2^-24 on average), or half the
+// spacing of the smallest fp16 numbers, 2^-25, where s x is small; with s max|x| >= 2^14 that is 2^-39 max|x|.  The
+// verdict demands that the largest value of every row and of every feature that is not all zero is at least
+// 2^-14 max|x|, so the absolute part stays below 2^-25 of the largest value of the row and of the feature.  The fp32
+// sums are the larger error: 3 roundings of a sum per 32 entries here, 8 with fp32 MFMAs.  b_u is summed with fp32
+// FMAs from the uncut values and ratings, as on the fp32 path, so ratings of any size are in range.
+// Measured ||A - A64|| / ||A64||, f = 100, 16 rows each, N(0, 0.3) / U(0, 1) factors (fp32 MFMA -> two parts):
+//     128 entries 1.8e-7 -> 1.3e-7 / 1.5e-7 -> 0.9e-7;  512: 3.5e-7 -> 2.6e-7 / 3.0e-7 -> 1.8e-7;
+//     4096: 9.7e-7 -> 7.6e-7 / 8.2e-7 -> 5.2e-7.
+// Rows with fewer than 64 entries (few sums, so the parts would be the larger error) and work items of more than 4096
+// entries (h l' is 2^-11 of a product: beyond 2^13 products it falls below the last bit of the sum) stay on fp32 MFMAs.
+#include "hermitian_kernels.h"
+
+namespace als {
+
+// maximum of non-negative floats as their bits, over the 16 lanes of a DPP row
+__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_umax(uint32_t v) {
+    return umax(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ uint32_t rowmax16(uint32_t v) {
+    return dpp_umax<0x140>(dpp_umax<0x141>(dpp_umax<0x4E>(dpp_umax<0xB1>(v))));
+}
+
+// The range of an n x F factor (F floats per row, rows 16-byte aligned): range[kRangeMax] = bits of max |x|,
+// range[kRangeWide] = 1 if two fp16 parts would not do (see above; also for a NaN or an infinity anywhere, and for a
+// factor so small that its scale would be clamped).  range[kRangeWork ..) are zero between launches: the last
+// workgroup to finish reads them and clears them.  16 lanes per row with the lane -> feature map of the gathers, four
+// rows of a lane in flight.  Bound: one pass over the factor (192 MB: 120 us, 1.6 TB/s).
+template <int F>
+__global__ __launch_bounds__(256) void k_factor_range(const float *__restrict__ G, int64_t n, uint32_t *__restrict__ range) {
+    constexpr int NT = tiles_1d(F), U = 4;
+    __shared__ uint32_t part[4][16 * NT], tot[4][2];
+    __shared__ int last;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, kq = lane >> 4;
+    uint32_t fm[NT], all = 0u, inv = 0u;   // inv: max of ~(largest value of a row), i.e. the smallest of them
+#pragma unroll
+    for (int q = 0; q < NT; ++q) fm[q] = 0u;
+    const int64_t stride = (int64_t)gridDim.x * 4 * (4 * U);
+    for (int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * (4 * U); r0 < n; r0 += stride) {
+        float g[U][NT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = r0 + 4 * u + kq;
+            gather_lane_features<F, ALS_F32>(G, (int)(r < n ? r : n - 1), i, g[u]);   // (n fits 31 bits)
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t m = 0u;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const uint32_t a = __builtin_bit_cast(uint32_t, g[u][q]) & 0x7fffffffu;
+                fm[q] = umax(fm[q], a);
+                m = umax(m, a);
+            }
+            m = rowmax16(m);
+            all = umax(all, m);
+            inv = umax(inv, m ? ~m : 0u);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        fm[q] = umax(fm[q], (uint32_t)__shfl_xor((int)fm[q], 16));
+        fm[q] = umax(fm[q], (uint32_t)__shfl_xor((int)fm[q], 32));
+        if (kq == 0) part[wave][16 * q + i] = fm[q];
+    }
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+        all = umax(all, (uint32_t)__shfl_xor((int)all, o));
+        inv = umax(inv, (uint32_t)__shfl_xor((int)inv, o));
+    }
+    if (lane == 0) { tot[wave][0] = all; tot[wave][1] = inv; }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 16 * NT; q += 256) {
+        const uint32_t v = umax(umax(part[0][q], part[1][q]), umax(part[2][q], part[3][q]));
+        if (v) atomicMax(range + kRangeFeatures + q, v);   // (filler lanes of the last tile stay zero)
+    }
+    if (threadIdx.x < 2) {
+        const int k = threadIdx.x;
+        atomicMax(range + kRangeWork + 1 + k, umax(umax(tot[0][k], tot[1][k]), umax(tot[2][k], tot[3][k])));
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(range + kRangeWork, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    __shared__ uint32_t word[2];
+    __shared__ int bad;
+    if (threadIdx.x < 2) word[threadIdx.x] = atomicExch(range + kRangeWork + 1 + threadIdx.x, 0u);
+    if (threadIdx.x == 2) bad = 0;
+    if (threadIdx.x == 3) atomicExch(range + kRangeWork, 0u);
+    __syncthreads();
+    const uint32_t mx = word[0], e = mx >> 23;
+    const float top = bits_to_float(mx), span = 16384.f;   // 2^14
+    bool out = mx != 0u && (e < 81u || e >= 255u || bits_to_float(~word[1]) * span < top);
+    for (int q = threadIdx.x; q < 16 * NT; q += 256) {
+        const uint32_t v = atomicExch(range + kRangeFeatures + q, 0u);
+        out |= v != 0u && bits_to_float(v) * span < top;
+    }
+    if (out) bad = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        range[kRangeMax] = mx;
+        range[kRangeWide] = (uint32_t)bad;
+    }
+}
+
+hipError_t launch_factor_range(int f, hipStream_t st, const float *G, int64_t n, uint32_t *range) {
+    if (n <= 0) return hipSuccess;
+    int64_t blocks = (n + 127) / 128;   // two rounds of 16 rows per wavefront; few workgroups, since each ends in atomics
+    blocks = blocks > 1024 ? 1024 : blocks;
+#define CALL(FF) hipLaunchKernelGGL(k_factor_range<FF>, dim3((unsigned)blocks), dim3(256), 0, st, G, n, range); break
+    switch (f) {
+        case 16: CALL(16);
+        case 32: CALL(32);
+        case 64: CALL(64);
+        case 100: CALL(100);
+        case 128: CALL(128);
+        case 256: CALL(256);
+        default: return hipErrorInvalidValue;
+    }
+#undef CALL
+    return hipGetLastError();
+}
+
+#define ALS_FOR_F(CALL)                       \
+    switch (f) {                              \
+        case 16: return CALL(16);             \
+        case 32: return CALL(32);             \
+        case 64: return CALL(64);             \
+        case 100: return CALL(100);           \
+        case 128: return CALL(128);           \
+        default: return hipErrorInvalidValue; \
+    }
+
+template <int F, typename PtrT>
+static hipError_t herm_auto_f(bool wide, bool s16, hipStream_t st, const int32_t *task_row, const int32_t *task_chunk,
+                            const int32_t *task_order, int64_t task0, int64_t ntasks, int chunk, const void *ptr,
+                            const int32_t *idx, const float *val, const void *Theta, float *slots, const uint32_t *range) {
+    if (ntasks <= 0) return hipSuccess;
+    const dim3 grid((unsigned)ntasks), block(64);
+    const PtrT *p = (const PtrT *)ptr;
+#define LAUNCH(W, S)                                                                                                  \
+    hipLaunchKernelGGL((k_hermitian<F, PtrT, W, kF32Auto, S, kExplicit>), grid, block, 0, st, task_row, task_chunk, \
+                       task_order, task0, chunk, p, idx, val, Theta, 0.f, slots, range)
+    if (wide) { if (s16) LAUNCH(true, true); else LAUNCH(true, false); }
+    else { if (s16) LAUNCH(false, true); else LAUNCH(false, false); }
+#undef LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_hermitian_auto(int f, bool ptr64, bool wide, bool s16, hipStream_t st, const int32_t *task_row,
+                               const int32_t *task_chunk, const int32_t *task_order, int64_t task0, int64_t ntasks,
+                               int chunk, const void *ptr, const int32_t *idx, const float *val, const void *Theta,
+                               float *slots, const uint32_t *range) {
+    if (f == 256) {
+        const hipError_t e = launch_hermitian_wide_auto(ptr64, wide, s16, st, task_row, task_chunk, task_order, task0, ntasks, chunk,
+                                                        ptr, idx, val, Theta, slots, range);
+        return e != hipSuccess ? e : launch_hermitian_wide(ptr64, wide, ALS_F32, s16, st, task_row, task_chunk, task_order, task0,
+                                                           ntasks, chunk, ptr, idx, val, Theta, slots, range);
+    }
+#define CALL(FF)                                                                                                      \
+    (ptr64 ? herm_auto_f<FF, int64_t>(wide, s16, st, task_row, task_chunk, task_order, task0, ntasks, chunk, ptr, idx, val, \
+                                    Theta, slots, range)                                                             \
+           : herm_auto_f<FF, int32_t>(wide, s16, st, task_row, task_chunk, task_order, task0, ntasks, chunk, ptr, idx, val, \
+                                    Theta, slots, range))
+    ALS_FOR_F(CALL)
+#undef CALL
+}
+
+template <int F, typename PtrT>
+static hipError_t herm_cg_auto_f(bool wide, int solver, hipStream_t st, const int32_t *perm, int64_t pos0, int64_t npos,
+                               const void *ptr, const int32_t *idx, const float *val, const void *Theta, float lambda,
+                               int fs, float eps, float *Xout, int *status, const uint32_t *range) {
+    if (npos <= 0) return hipSuccess;
+    const dim3 grid((unsigned)npos), block(64);
+    const PtrT *p = (const PtrT *)ptr;
+#define LAUNCH(W, S)                                                                                                  \
+    hipLaunchKernelGGL((k_hermitian_cg<F, PtrT, W, kF32Auto, S, kExplicit>), grid, block, 0, st, perm, pos0, p, idx, val, \
+                       Theta, lambda, 0.f, (const float *)nullptr, fs, eps, Xout, status, range)
+    if (solver == ALS_SOLVER_CG) { if (wide) LAUNCH(true, ALS_SOLVER_CG); else LAUNCH(false, ALS_SOLVER_CG); }
+    else { if (wide) LAUNCH(true, ALS_SOLVER_CHOLESKY); else LAUNCH(false, ALS_SOLVER_CHOLESKY); }
+#undef LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_hermitian_cg_auto(int f, bool ptr64, bool wide, int solver, hipStream_t st, const int32_t *perm,
+                                  int64_t pos0, int64_t npos, const void *ptr, const int32_t *idx, const float *val,
+                                  const void *Theta, float lambda, int fs, float eps, float *Xout, int *status, const uint32_t *range) {
+    if (f == 256) {   // Algorithm 1 only: the exact solver at this width stays on the fp32 kernels
+        if (solver != ALS_SOLVER_CG) return hipErrorInvalidValue;
+        const hipError_t e = launch_hermitian_cg_wide_auto(ptr64, wide, st, perm, pos0, npos, ptr, idx, val, Theta, lambda, fs, eps,
+                                                           Xout, status, range);
+        return e != hipSuccess ? e : launch_hermitian_cg_wide(f, ptr64, wide, ALS_F32, st, perm, pos0, npos, ptr, idx, val, Theta,
+                                                              lambda, fs, eps, Xout, status, range);
+    }
+#define CALL(FF)                                                                                                      \
+    (ptr64 ? herm_cg_auto_f<FF, int64_t>(wide, solver, st, perm, pos0, npos, ptr, idx, val, Theta, lambda, fs, eps, Xout, \
+                                       status, range)                                                                \
+           : herm_cg_auto_f<FF, int32_t>(wide, solver, st, perm, pos0, npos, ptr, idx, val, Theta, lambda, fs, eps, Xout, \
+                                       status, range))
+    ALS_FOR_F(CALL)
+#undef CALL
+}
+
+}  // namespace als

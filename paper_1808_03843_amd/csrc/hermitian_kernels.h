@@ -22,10 +22,13 @@ constexpr int kDepthSlots = ALS_DEPTH_SLOTS, kDepthFused = ALS_DEPTH_FUSED;
 // (f = 128 with 16-bit inputs: the operand sets of 32 entries and the extra b_u tiles need the whole file)
 constexpr int fused_waves(int F, int ET = ALS_F32, int MODE = kExplicit) {
     if (ET == ALS_F32X3) return F <= 100 ? 2 : 1;   // three operand sets of 32 entries beside the accumulators
-    if (ET == ALS_F32X2) return F <= 100 ? 2 : 1;   // two operand sets (f = 128: 144 accumulator registers)
+    if (ET == ALS_F32X2 || ET == kF32Auto) return F <= 100 ? 2 : 1;   // two operand sets (f = 128: 144 accumulator registers)
     if ((ET == ALS_BF16 || ET == ALS_F16) && MODE == kImplicit && F > 64) return 1;   // likewise: w * theta in three parts
     return F <= 100 ? ALS_FUSED_WAVES : (ET != ALS_F32 ? 1 : 2);
 }
+
+// and the most: narrow systems need few registers, and the wavefronts that then fit hide the latency of the gathers
+constexpr int fused_waves_max(int F, int ET = ALS_F32, int MODE = kExplicit) { return F <= 64 ? 8 : fused_waves(F, ET, MODE); }
 
 // 16-bit factor inputs go to the 16-bit matrix cores where the width allows it (tiles16.h)
 constexpr bool use_tiles16(int F, int ET, int MODE) {
@@ -36,7 +39,7 @@ constexpr bool use_tiles16(int F, int ET, int MODE) {
 // otherwise lands just above the register budget of two and then spreads out to one
 constexpr int slot_waves(int F, int ET, int MODE = kExplicit) {
     if (ET == ALS_F32X3) return F <= 100 ? 2 : 1;   // rows staged through LDS: two wavefronts fit
-    if (ET == ALS_F32X2) return F <= 100 ? 2 : 1;
+    if (ET == ALS_F32X2 || ET == kF32Auto) return F <= 100 ? 2 : 1;
     return (F == 100 && (ET == ALS_BF16 || ET == ALS_F16) && MODE == kExplicit) ? 2 : 1;
 }
 
@@ -45,6 +48,19 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// ET = kF32Auto: one of the two loops for fp32 factors, by the verdict of k_factor_range (the same for all wavefronts)
+template <int F, bool WIDE, int D>
+__device__ __forceinline__ void accumulate_auto(const int32_t *__restrict__ idx, const float *__restrict__ val,
+                                                const void *__restrict__ Theta, int64_t s0, int len,
+                                                v4f (&acc)[tiles_tri(F)], float (&b)[tiles_1d(F)], const uint32_t *range) {
+    __shared__ __attribute__((aligned(16))) uint32_t fifo[x3_fifo_words(F)];   // one wavefront per workgroup
+    const uint32_t mx = __builtin_amdgcn_readfirstlane(range[kRangeMax]);
+    if (__builtin_amdgcn_readfirstlane(range[kRangeWide]) == 0u)
+        accumulate_tiles_x3<F, WIDE, true, rows_all(F), 2, true>(idx, val, Theta, s0, len, acc, b, fifo, mx);
+    else
+        accumulate_tiles<F, true, D, WIDE, ALS_F32>(idx, val, Theta, s0, len, acc, b);
 }
 
 // MODE: kExplicit (eq. (2)) or kImplicit (Section 5.6: every stored entry weighted by alpha * r_uv, b_u by
@@ -80,6 +96,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(slot_waves(F
         accumulate_tiles_x3<F, WIDE, true, rows_all(F), ET == ALS_F32X3 ? 3 : 2>(idx, val, Theta, uniform64(s0), len, acc, b,
                                                                                    fifo, mx);
     }
+    else if constexpr (ET == kF32Auto)
+        accumulate_auto<F, WIDE, kDepthSlots>(idx, val, Theta, uniform64(s0), len, acc, b, absmax);
     else if constexpr (use_tiles16(F, ET, MODE))
         accumulate_tiles16<F, WIDE, ET, true, rows_all(F), MODE>(idx, val, Theta, uniform64(s0), len, acc, b, alpha);
     else
@@ -148,7 +166,7 @@ __device__ __forceinline__ void load_tiles(const float *__restrict__ src, v4f (&
 
 // gram (kImplicit only): tiles of Theta^T Theta, the starting value of the accumulators
 template <int F, typename PtrT, bool WIDE, int ET, int SOLVER, int MODE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(fused_waves(F, ET, MODE), fused_waves(F, ET, MODE)))) void k_hermitian_cg(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(fused_waves(F, ET, MODE), fused_waves_max(F, ET, MODE)))) void k_hermitian_cg(
     const int32_t *__restrict__ perm, int64_t pos0, const PtrT *__restrict__ ptr, const int32_t *__restrict__ idx,
     const float *__restrict__ val, const void *__restrict__ Theta, float lambda, float alpha,
     const float *__restrict__ gram, int fs, float eps, float *__restrict__ Xout, int *__restrict__ status,
@@ -177,6 +195,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(fused_waves(
         accumulate_tiles_x3<F, WIDE, true, rows_all(F), ET == ALS_F32X3 ? 3 : 2>(idx, val, Theta, uniform64(s0), len, acc, b,
                                                                                    fifo, mx);
     }
+    else if constexpr (ET == kF32Auto)
+        accumulate_auto<F, WIDE, kDepthFused>(idx, val, Theta, uniform64(s0), len, acc, b, absmax);
     else if constexpr (use_tiles16(F, ET, MODE))
         accumulate_tiles16<F, WIDE, ET, true, rows_all(F), MODE>(idx, val, Theta, uniform64(s0), len, acc, b, alpha);
     else

@@ -9,12 +9,17 @@
 // Layout as in tiles16.h: one step consumes 32 stored entries, lane (i, kq) supplies its feature of the 8 entries
 // 8kq .. 8kq+7, packed in pairs; the parts of a value sit at the same place of two or three operand registers.
 //
-// Last tile row (f = 100: 4 features): its A operand stacks the parts, lanes 0-3 the first parts of the 4 features,
-// 4-7 the second, 8-11 the third, and lanes 12 .. the parts of the rating.  Multiplied with each part of a tile column
-// (3 MFMAs instead of 6 with three parts, 2 instead of 3 with two), rows k, 4+k and 8+k of the result add up to row k
-// of the strip and the rows from 12 on add up to b_u, with all part products included.  147 and 77 MFMAs a step
-// instead of 168 and 84.  When f is a multiple of 16 the parts of the rating form an operand of their own (lanes
-// 0..2) that is multiplied with all parts of every tile column, and rows 0..2 of these extra tiles add up to b_u.
+// b_u with three parts: when f is not a multiple of 16 the lane i = f % 16 of the last tile carries the fp32 rating
+// instead of a feature and is cut into parts like everything else, so row f of the accumulated matrix is b_u to the same
+// accuracy; the lanes beyond it carry zeros.  When f is a multiple of 16 the parts of the rating form an operand of their
+// own (lanes 0..2) that is multiplied with all parts of every tile column, and rows 0..2 of these extra tiles add up to b_u.
+// Two parts at f = 100 (a last tile of 4 features): the A operand of the last tile row stacks the parts, lanes 0-3 the
+// first and 4-7 the second parts of the 4 features, lanes 12 and 13 those of the rating.  Multiplied with each part of a
+// tile column (2 MFMAs instead of 3), rows k and 4+k of the result add up to row k of the strip and rows 12 and 13 to b_u,
+// with all part products included: 77 MFMAs a step instead of 84.  (Not with three parts: the products with a third
+// part fall below the last bit of sums over thousands of entries, everywhere by the same factor as long as all rows
+// are accumulated alike, which cancels in A_u^-1 b_u; stacked rows keep them, and that was worse: Large-square, five
+// exact sweeps, stored rows 8.6e-4 off instead of below 5e-4.)
 //
 // The gathered rows are staged through LDS (Section 3: the rows of Theta that a row of R refers to are staged on
 // chip in batches).  Why: the operands of a step (three parts of 32 entries: 84 registers at f = 100) and the 112
@@ -28,7 +33,7 @@
 // and 4 bytes; rows 8 apart start 32 banks apart at f = 100).  The buffer is refilled once the step has read it all;
 // the loads then run under the step's MFMAs.
 // Measured (Mid shape, CG(6), ms per sweep, against the lane-mapped loads): two parts f = 32 4.97 -> 3.51, f = 100
-// 11.6 -> 11.3; three parts f = 100 14.9 -> 14.3; f = 64 and 128 unchanged (their rows were whole 16-byte loads before).
+// 11.6 -> 11.3; three parts f = 100 14.9 -> 14.6; f = 64 and 128 unchanged (their rows were whole 16-byte loads before).
 // Column side at f = 100, two parts: 3.1 ms = the 6.4 TB/s at which rows of X arrive from beyond the L2.
 #pragma once
 #include "tiles16.h"
@@ -43,6 +48,30 @@ constexpr int x3_fifo_words(int F) { return x3_loads(F) * 256; }
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef const __attribute__((address_space(1))) void global_void;
+
+// the power-of-two scale of the two-part route and its inverse, from the bits of max |Theta| (uniform: scalar registers)
+__device__ __forceinline__ void two_part_scale(uint32_t absmax_bits, float &scale, float &inv_scale) {
+    const uint32_t e = (absmax_bits >> 23) & 0xffu;
+    uint32_t se = (e == 0u || e == 255u) ? 127u : 268u - e;   // s * max in [2^14, 2^15)
+    se = se > 187u ? 187u : se;                               // (a factor of all-tiny values: s stays at 2^60)
+    scale = bits_to_float(se << 23);
+    inv_scale = bits_to_float((254u - se) << 23);
+}
+
+// two scaled values -> their first parts and their second parts, packed.  s x - h is exact in fp32 (s is a power of two):
+// one mixed-precision fma per part and value, which rounds the product, or the difference, to fp16.  (The empty
+// statement keeps the packed first parts in one register: the compiler would otherwise form them a second time for
+// the difference.)
+__device__ __forceinline__ void split_two(float x0, float x1, float scale, uint32_t &h, uint32_t &l) {
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    uint32_t hp = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, 0.f),
+                                                      (_Float16)__builtin_fmaf(x1, scale, 0.f)});
+    asm("" : "+v"(hp));
+    const v2h hh = __builtin_bit_cast(v2h, hp);
+    h = hp;
+    l = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, -(float)hh.x),
+                                           (_Float16)__builtin_fmaf(x1, scale, -(float)hh.y)});
+}
 
 // PARTS = 2 (factor_dtype = ALS_F32X2): the value is cut into two fp16 parts instead, h = fp16(s x) and
 // l = fp16(s x - h), both rounded to nearest, so |s x - (h + l)| <= 2^-22 |s x|; a product is the three fp16 products
@@ -63,19 +92,12 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     static_assert(ROWS == rows_all(F) || (F % 16) == 0, "partial sets of tile rows need f to be a multiple of 16");
     static_assert(PARTS == 2 || PARTS == 3, "two fp16 parts or three bf16 parts");
     constexpr int PT = PARTS == 3 ? ALS_BF16 : ALS_F16;   // element type of the parts
-    // the power-of-two scale of the two-part route (uniform: scalar registers)
     float scale = 1.f, inv_scale = 1.f;
-    if constexpr (PARTS == 2) {
-        const uint32_t e = (absmax_bits >> 23) & 0xffu;
-        uint32_t se = (e == 0u || e == 255u) ? 127u : 268u - e;   // s * max in [2^14, 2^15)
-        se = se > 187u ? 187u : se;                               // (a factor of all-tiny values: s stays at 2^60)
-        scale = bits_to_float(se << 23);
-        inv_scale = bits_to_float((254u - se) << 23);
-    }
+    if constexpr (PARTS == 2) two_part_scale(absmax_bits, scale, inv_scale);
     constexpr int NT = tiles_1d(F), RI = F % 16;
     constexpr bool BX = RI == 0;   // the rating parts are an operand of their own
-    constexpr bool STACK = RI > 0 && RI <= 4;   // last tile row: the parts stacked in one operand (see above)
-    static_assert(BX || STACK, "a partial last tile of more than 4 features is not needed by any supported f");
+    constexpr bool STACK = RI > 0 && PARTS == 2;   // last tile row: the parts stacked in one operand (see above)
+    static_assert(RI <= 4, "a partial last tile of more than 4 features is not needed by any supported f");
     constexpr int N4 = loads16(F), N2 = loads8(F), N1 = loads4(F);
     constexpr int base1 = 64 * N4 + 32 * N2, first1 = 4 * N4 + 2 * N2;
     constexpr int LB = (NT - 1) * NT / 2;
@@ -133,11 +155,12 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     using G1 = std::integral_constant<int, 1>;
     using G2 = std::integral_constant<int, 2>;
 
-    // STACK: lanes 0-3, 4-7, 8-11 carry the first, second and third part of the features (two parts: lanes 8-11 zero),
-    // lane 12 + k part k of the rating, the others zero
+    // STACK: lanes 0-3 and 4-7 carry the first and second part of the features, lane 12 + k part k of the rating, the
+    // others zero; otherwise lane i < RI its feature, lane RI the rating
     const int part = i < 12 ? i >> 2 : i - 12;
-    const bool is_rating = !FMA_B && i >= 12 && part < PARTS, is_feat = i < 4 * PARTS && (i & 3) < RI;
-    const bool part1 = part == 1, part2 = part == 2;
+    const bool is_rating = !FMA_B && (STACK ? (i >= 12 && part < PARTS) : i == RI);
+    const bool is_feat = STACK ? (i < 4 * PARTS && (i & 3) < RI) : i < RI;
+    const bool part1 = part == 1;
     const bool is_r0 = i == 0, is_r1 = i == 1, is_r2 = i == 2;
     float bacc[FMA_B ? NT : 1];   // FMA_B: this lane's share of b_u
 #pragma unroll
@@ -174,20 +197,14 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
             m[T][pr] = split16<ALS_BF16>(x0, x1);
             l[T][pr] = split16<ALS_BF16>(x0, x1);
         } else {
-            // s x - h is exact in fp32 (s is a power of two): one mixed-precision fma per part and value, which rounds
-            // the product, or the difference, to fp16.  (The empty statement keeps the packed first parts in one
-            // register: the compiler would otherwise form them a second time for the difference.)
-            uint32_t hp = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, 0.f),
-                                                              (_Float16)__builtin_fmaf(x1, scale, 0.f)});
-            asm("" : "+v"(hp));
-            const v2h hh = __builtin_bit_cast(v2h, hp);
+            uint32_t hp, lp;
+            split_two(x0, x1, scale, hp, lp);
             h[T][pr] = hp;
-            l[T][pr] = __builtin_bit_cast(uint32_t, (v2h){(_Float16)__builtin_fmaf(x0, scale, -(float)hh.x),
-                                                          (_Float16)__builtin_fmaf(x1, scale, -(float)hh.y)});
+            l[T][pr] = lp;
         }
         if constexpr (STACK && T == NT - 1) {
-            const uint32_t p0 = h[T][pr], p1 = PARTS == 3 ? m[PARTS == 3 ? T : 0][pr] : l[T][pr], p2 = l[T][pr];
-            gr[pr] = PARTS == 3 && part2 ? p2 : (part1 ? p1 : p0);
+            const uint32_t p0 = h[T][pr], p1 = l[T][pr];
+            gr[pr] = part1 ? p1 : p0;
         }
     };
     // reads the rows back, one entry pair at a time, and cuts the tiles of group G (the 16-, 8- and 4-byte parts of a
@@ -256,7 +273,6 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
                     if constexpr (STACK) {
                         if (R == NT - 1) {
                             mfma_16x16x32<PT>(a, gr, l[C]);
-                            if constexpr (PARTS == 3) mfma_16x16x32<PT>(a, gr, m[C]);
                             mfma_16x16x32<PT>(a, gr, h[C]);
                             continue;
                         }
@@ -311,40 +327,41 @@ __device__ __forceinline__ void accumulate_tiles_x3(const int32_t *__restrict__ 
     for (int t = 0; t + 1 < nsteps; ++t) step(std::false_type{}, t);
     step(std::true_type{}, nsteps - 1);
 
-    // b_u = rows 12 .. of the stacked last tile row, or rows 0 .. 2 of the extra tiles
+    // b_u = rows 12, 13 of the stacked last tile row, row RI of the plain one, or rows 0 .. 2 of the extra tiles
     const int c = i, g4 = kq;
     if constexpr (WANT_B && FMA_B) {
 #pragma unroll
         for (int T = 0; T < NT; ++T) b[T] = (((ROWS >> T) & 1u) && (BX || T < NT - 1 || c < RI)) ? colsum4(bacc[T]) : 0.f;
     } else if constexpr (WANT_B) {
-        constexpr int first_lane = STACK ? 48 : 0;   // the lane row that holds them, in registers 0 .. PARTS - 1
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
             float s;
-            if constexpr (STACK) s = PARTS == 3 ? acc[LB + T][0] + acc[LB + T][1] + acc[LB + T][2] : acc[LB + T][0] + acc[LB + T][1];
-            else s = PARTS == 3 ? bt[T][0] + bt[T][1] + bt[T][2] : bt[T][0] + bt[T][1];
-            s = bperm(4 * (first_lane + c), s);
+            if constexpr (STACK) s = bperm(4 * (48 + c), acc[LB + T][0] + acc[LB + T][1]);
+            else if constexpr (!BX) s = bperm(4 * (16 * (RI / 4) + c), acc[LB + T][RI % 4]);   // lane row RI/4, register RI%4
+            else s = bperm(4 * c, PARTS == 3 ? bt[T][0] + bt[T][1] + bt[T][2] : bt[T][0] + bt[T][1]);
             if constexpr (PARTS == 2) s *= inv_scale;   // sum of r * (s theta)
             b[T] = (((ROWS >> T) & 1u) && (BX || T < NT - 1 || c < RI)) ? s : 0.f;
         }
     }
-    if constexpr (STACK) {   // rows k, 4 + k and 8 + k of the last tile row add up to feature row k; the rest is padding
-        const int a16 = 4 * (lane ^ 16), a32 = 4 * (lane ^ 32);
+    if constexpr (STACK) {   // rows k and 4 + k of the last tile row add up to feature row k; the rest is padding
+        const int a16 = 4 * (lane ^ 16);
 #pragma unroll
         for (int T = 0; T < NT; ++T) {
             v4f &a = acc[LB + T];
             float t[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = g4 < PARTS ? a[r] : 0.f;
-#pragma unroll
             for (int r = 0; r < 4; ++r) t[r] = bperm(a16, a[r]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] += t[r];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) t[r] = bperm(a32, a[r]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) a[r] = (g4 == 0 && r < RI && (T < NT - 1 || c < RI)) ? a[r] + t[r] : 0.f;
         }
+    } else if constexpr (!BX) {
+#pragma unroll
+        for (int T = 0; T < NT; ++T)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool keep = (4 * g4 + r < RI) && (T < NT - 1 || c < RI);
+                acc[LB + T][r] = keep ? acc[LB + T][r] : 0.f;
+            }
     }
     if constexpr (PARTS == 2) {   // sums of (s theta)(s theta'): back to the caller's scale, exactly
         const float inv2 = inv_scale * inv_scale;

@@ -3,6 +3,11 @@
 #include <utility>
 
 #include "hermitian_kernels.h"
+// steps that the gathers of the shared two-part loop run ahead
+#ifndef ALS_X2_SHARED_DEPTH
+#define ALS_X2_SHARED_DEPTH 2
+#endif
+#include "tiles_x2_shared.h"
 
 namespace als {
 
@@ -33,6 +38,10 @@ constexpr int kWideEu = ALS_WIDE_EU, kDepthWide = ALS_DEPTH_WIDE;
 constexpr int wide_eu(int ET, int MODE = kExplicit) {
     return (ET == ALS_F32 && MODE == kExplicit) ? kWideEu : (kWideEu > 2 ? 2 : kWideEu);
 }
+
+// (the shared two-part loop: with a budget of exactly two the scheduler runs into spills, without one it needs about 160
+// registers)
+constexpr int wide_eu_max(int ET, int MODE = kExplicit) { return ET == kF32Auto ? 4 : wide_eu(ET, MODE); }
 
 // fn(integral_constant<w>) for the (wavefront-uniform) w == wave
 template <int NW, typename Fn>
