@@ -6,7 +6,7 @@
 // Why: fp32 MFMAs run at 1/16 of the rate of the 16-bit ones and share the issue port with the vector ALU, so the fp32
 // loop is bound by them (k_hermitian 112 of 141 TFLOP/s).  Two parts take 3 (77 MFMAs a step of 32 entries at
 // f = 100) where fp32 takes 8 x 28: Mid shape, CG(6), ms per sweep
-// f = 16 3.45 -> 2.18, 32 4.34 -> 2.67, 64 9.06 -> 5.40, 100 18.9 -> 11.5, 128 28.1 -> 17.0; 120,047 x 17,771 with 25M entries, exact,
+// f = 16 3.45 -> 2.18, 32 4.34 -> 2.67, 64 9.06 -> 5.40, 100 18.9 -> 11.5, 128 28.1 -> 16.1; 120,047 x 17,771 with 25M entries, exact,
 // f = 100 7.3 -> 5.0; the scan included.
 //
 // Accuracy.  A value s x = h + l + d has |d| <= 2^-22 |s x| (rounded to nearest twice: 2^-24 on average), or half the
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void k_factor_range(const float *__restrict__ 
 hipError_t launch_factor_range(int f, hipStream_t st, const float *G, int64_t n, uint32_t *range) {
     if (n <= 0) return hipSuccess;
     int64_t blocks = (n + 127) / 128;   // two rounds of 16 rows per wavefront; few workgroups, since each ends in atomics
-    blocks = blocks > 1024 ? 1024 : blocks;
+    blocks = blocks > 512 ? 512 : blocks;
 #define CALL(FF) hipLaunchKernelGGL(k_factor_range<FF>, dim3((unsigned)blocks), dim3(256), 0, st, G, n, range); break
     switch (f) {
         case 16: CALL(16);

@@ -1,6 +1,6 @@
-"""fp32 factors (factor_dtype = F32, f <= 128, explicit feedback, a quarter of a million entries and more): rows of 64 and
-more entries are multiplied as two fp16 parts per value where the range of the gathered factor allows it, and on the
-fp32 matrix instructions otherwise.  Held to the bars of the fp32 path; the verdict on the range at its edges."""
+"""fp32 factors (factor_dtype = F32, explicit feedback, a quarter of a million entries and more): rows of 64 and more entries
+are multiplied as two fp16 parts per value where the range of the gathered factor allows it, and on the fp32 matrix
+instructions otherwise.  Held to the bars of the fp32 path; the verdict on the range at its edges."""
 import numpy as np
 import pytest
 
@@ -24,7 +24,7 @@ def P():
 @pytest.fixture(scope="module")
 def mat():
     rng = np.random.default_rng(71)
-    deg = np.array(EDGES + [300] * 800 + [64, 65, 79, 96] * 4)        # > 2^18 entries
+    deg = np.array(EDGES + [300] * 800 + [64, 65, 79, 96, 511, 512, 513] * 4)        # > 2^18 entries
     ptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
     assert ptr[-1] >= 1 << 18
     idx = np.concatenate([np.sort(rng.choice(N, d, replace=False)) for d in deg]).astype(np.int32)
@@ -46,7 +46,7 @@ def _update(P, mat, Theta, f, solver, chunk=0, p64=False, lam=0.3, warm=None, s1
     return als, sp, X
 
 
-@pytest.mark.parametrize("f", [16, 32, 64, 100, 128])
+@pytest.mark.parametrize("f", [16, 32, 64, 100, 128, 256])
 @pytest.mark.parametrize("solver,p64", [("cholesky", False), ("cholesky", True), ("cg", False)])
 def test_half_sweep_against_the_oracle(P, mat, f, solver, p64):
     deg, ptr, idx, val = mat
@@ -82,12 +82,14 @@ RANGES = [("ordinary", None, True), ("row", 2.0 ** -14, True), ("row", 2.0 ** -1
           ("all", 2.0 ** -60, False), ("all", 2.0 ** 40, True), ("inf", None, False)]
 
 
-@pytest.mark.parametrize("f", [16, 100])
+@pytest.mark.parametrize("f", [16, 100, 256])
 @pytest.mark.parametrize("kind,scale,taken", RANGES)
 @pytest.mark.parametrize("at", [0, N - 1])
 def test_verdict_on_the_range_of_the_factor(P, mat, f, kind, scale, taken, at):
     """Where two parts are refused, rows shorter than a work item are bit for bit those of a context that never takes
     them (work items of 8192 entries); where they are taken, they are not."""
+    if f == 256 and kind == "all":
+        pytest.skip("needs the exact solver, whose short rows stay on fp32 matrix instructions at this width")
     deg, ptr, idx, val = mat
     Theta = _theta(f)
     Theta[7, 3] = 2.0                                # the largest value
@@ -106,7 +108,7 @@ def test_verdict_on_the_range_of_the_factor(P, mat, f, kind, scale, taken, at):
     a, _, X = _update(P, mat, Theta, f, solver, lam=lam)
     b, _, Y = _update(P, mat, Theta, f, solver, chunk=8192, lam=lam)
     torch.cuda.synchronize()
-    long = torch.from_numpy((deg >= 128) & (deg < 4096)).cuda()
+    long = torch.from_numpy((deg >= 128) & (deg < 512)).cuda()          # one work item each in both contexts
     same = torch.equal(torch.nan_to_num(X[long], nan=7.5), torch.nan_to_num(Y[long], nan=7.5))
     assert same == (not taken)
     if kind == "inf":
@@ -129,7 +131,7 @@ def test_error_is_no_larger_than_that_of_fp32_matrix_instructions(P, mat):
     s, e = ptr[first], ptr[first + 800]
     ref = oracle.update_rows(ptr[first:first + 801] - s, idx[s:e], val[s:e], Theta, lam)
     err = []
-    for chunk in (4096, 8192):
+    for chunk in (0, 8192):
         als, _, X = _update(P, mat, Theta, f, P.SOLVER_CHOLESKY, chunk=chunk, lam=lam)
         als.synchronize()
         als.close()
