@@ -108,8 +108,8 @@ typedef struct als_config {
     int32_t device;       /* HIP device ordinal                                                          */
     void *stream;         /* hipStream_t to enqueue on (NULL = the default stream)                       */
     int32_t chunk;        /* stored entries per work item, a power of two in [64, 2^20]; longer rows are
-                             split.  0 (default): 4096, and 512 .. 2048 for matrices of 2^18 .. 2^25 stored
-                             entries, which 4096 would leave in too few work items                       */
+                             split.  0 (default): 4096, and with explicit feedback 512 .. 2048 for matrices of
+                             2^18 .. 2^25 stored entries, which 4096 would leave in too few work items    */
     int64_t batch_slots;  /* work items whose partial A_u are held at once (0 = about 4 GB worth;
                              larger values than 4,194,303 are taken as that)                                      */
     int32_t profile;      /* 1: bracket every kernel with HIP events (see als_kernel_time)               */
@@ -240,8 +240,8 @@ int als_bin_rows(als_ctx *ctx, const als_sparse *csr, int nclass, int32_t *perm_
  * about 16 bytes per entry of temporary device memory (4 when the column ids
  * fit into 10 bits) plus at most half a byte per entry of counters, and waits
  * for the result.  Without a caller's workspace the context keeps that memory
- * for further calls, if it is no more than 2 GiB, until the next call that builds
- * a work plan (64 MiB of it until als_destroy). */
+ * for further calls, if it is no more than 2 GiB, until als_drop_plans or
+ * als_destroy. */
 int als_csr_to_csc(als_ctx *ctx, const als_sparse *csr, void *cptr_out, int32_t *cidx_out, float *cval_out);
 
 /* Waits for the stream and reports ALS_ENUMERIC if any kernel since the last
@@ -276,7 +276,8 @@ int als_short_row_limit(const als_ctx *ctx);
  * and nnz and holds its degree classes and work items, so the arrays of a matrix must stay unchanged between
  * calls; call this after changing them in place, or when a different matrix with the same nrows and nnz may have
  * been allocated at the address of an earlier one (the kernels stay inside the arrays with a stale plan, but
- * the results are wrong; als_synchronize reports it).  The next call on any matrix rebuilds its plan. */
+ * the results are wrong; als_synchronize reports it).  The next call on any matrix rebuilds its plan.  Also
+ * gives back the memory kept by als_csr_to_csc. */
 int als_drop_plans(als_ctx *ctx);
 
 /* Kernel ids for als_kernel_time */

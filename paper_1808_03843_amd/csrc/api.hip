@@ -39,8 +39,11 @@ constexpr int kDefaultChunk = 4096;
 struct ChunkBySize { int64_t below; int chunk; };
 constexpr ChunkBySize kChunkBySize[] = {
     {1ll << 18, kDefaultChunk}, {1ll << 21, 512}, {1ll << 23, 1024}, {1ll << 25, 2048}, {INT64_MAX, kDefaultChunk}};
-int chunk_of(const als_config &c, int64_t nnz) {
+// Implicit feedback keeps 4096: after a sweep the rows of a factor share a direction, and the six steps of Algorithm 1 turn
+// another order of the sums into differences of 1e-3 in the next one.
+int chunk_of(const als_config &c, int64_t nnz, bool implicit = false) {
     if (c.chunk != 0) return c.chunk;
+    if (implicit) return kDefaultChunk;
     for (const auto &r : kChunkBySize)
         if (nnz < r.below) return r.chunk;
     return kDefaultChunk;
@@ -127,7 +130,7 @@ bool two_part_route(const als_config &c, const als_sparse *a) {
 
 // Allocating and freeing the 1.6 GB that 99M entries take costs about as much as sorting them (1.4 against 2.4 ms), and far
 // more in a tight loop, where every fresh allocation waits for the memory to be cleared
-constexpr size_t kSortKeep = (size_t)2 << 30, kSortSmall = (size_t)64 << 20;   // (up to 64 MB stay until als_destroy)
+constexpr size_t kSortKeep = (size_t)2 << 30;
 
 struct TimedLaunch { hipEvent_t a, b; int kernel; };
 }  // namespace
@@ -142,7 +145,7 @@ struct als_ctx {
     size_t slots_bytes = 0;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
-    void *sort_scratch = nullptr;   // als_csr_to_csc: kept between its calls up to kSortKeep bytes, given back by the next plan build beyond kSortSmall
+    void *sort_scratch = nullptr;   // als_csr_to_csc: kept between its calls up to kSortKeep bytes, given back by als_drop_plans and als_destroy
     size_t sort_scratch_bytes = 0;
     int *status = nullptr;       // DEVICE status word
     int *check_flags = nullptr;  // DEVICE: result word of als_check_matrix
@@ -215,10 +218,22 @@ void free_sort_scratch(als_ctx *ctx) {
     ctx->sort_scratch_bytes = 0;
 }
 
+// hipMalloc that gives the memory kept by als_csr_to_csc back before it fails
+template <typename T>
+hipError_t device_alloc(als_ctx *ctx, T **out, size_t bytes) {
+    hipError_t e = hipMalloc(out, bytes);
+    if (e == hipErrorOutOfMemory && ctx->sort_scratch) {
+        (void)hipGetLastError();
+        free_sort_scratch(ctx);
+        e = hipMalloc(out, bytes);
+    }
+    return e;
+}
+
 // device memory of a plan: a piece of the arena (workspace mode; the caller has made sure the plan fits) or hipMalloc
 template <typename T>
 hipError_t plan_alloc(als_ctx *ctx, T **out, size_t bytes) {
-    if (!ctx->fixed) return hipMalloc(out, bytes);
+    if (!ctx->fixed) return device_alloc(ctx, out, bytes);
     if (ctx->arena_used + aligned(bytes) > ctx->arena_bytes) return hipErrorOutOfMemory;
     *out = reinterpret_cast<T *>(ctx->arena + ctx->arena_used);
     ctx->arena_used += aligned(bytes);
@@ -277,12 +292,13 @@ struct Timed {   // brackets one launch with events when profiling is on
     }
 };
 
-int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p);
+int build_plan(als_ctx *ctx, const als_sparse *a, int chunk, Plan &p);
 
 // Finds or builds the plan of a matrix: degree-class permutation, work items, launch order of the slot work items.
-int get_plan(als_ctx *ctx, const als_sparse *a, Plan **out) {
+int get_plan(als_ctx *ctx, const als_sparse *a, bool implicit, Plan **out) {
+    const int chunk = chunk_of(ctx->cfg, a->nnz, implicit);
     for (auto &p : ctx->plans)
-        if (p.key_ptr == a->ptr && p.nrows == a->nrows && p.nnz == a->nnz) {
+        if (p.key_ptr == a->ptr && p.nrows == a->nrows && p.nnz == a->nnz && p.chunk == chunk) {
             *out = &p;
             return ALS_OK;
         }
@@ -303,9 +319,8 @@ int get_plan(als_ctx *ctx, const als_sparse *a, Plan **out) {
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         free_plan(ctx, p);
     }
-    if (ctx->sort_scratch_bytes > kSortSmall) free_sort_scratch(ctx);
     const size_t arena_mark = ctx->arena_used;
-    const int rc = build_plan(ctx, a, p);
+    const int rc = build_plan(ctx, a, chunk, p);
     if (rc != ALS_OK) {   // nothing of a half-built plan stays behind
         (void)hipStreamSynchronize(ctx->stream);
         free_plan(ctx, p);
@@ -355,11 +370,11 @@ int build_order(als_ctx *ctx, const als_sparse *a, Plan &p) {
     return ALS_OK;
 }
 
-int build_plan(als_ctx *ctx, const als_sparse *a, Plan &p) {
+int build_plan(als_ctx *ctx, const als_sparse *a, int chunk, Plan &p) {
     Timed timed(ctx, ALS_K_PLAN);
     const int64_t m = a->nrows;
     const bool p64 = a->ptr_is_64 != 0;
-    p.chunk = chunk_of(ctx->cfg, a->nnz);
+    p.chunk = chunk;
     HIP_TRY(ctx, plan_alloc(ctx, &p.perm, sizeof(int32_t) * (size_t)(m > 0 ? m : 1)));
     HIP_TRY(ctx, plan_alloc(ctx, &p.task_off, sizeof(int32_t) * (size_t)(m + 1)));
     int32_t *class_start_dev = ctx->class_start_dev;
@@ -433,7 +448,7 @@ int ensure_slots(als_ctx *ctx, int64_t nslots, bool s16) {
         HIP_TRY(ctx, hipFree(ctx->slots));
         ctx->slots = nullptr; ctx->slots_bytes = 0;
     }
-    HIP_TRY(ctx, hipMalloc(&ctx->slots, need));
+    HIP_TRY(ctx, device_alloc(ctx, &ctx->slots, need));
     ctx->slots_bytes = need;
     return ALS_OK;
 }
@@ -500,7 +515,7 @@ int update(als_ctx *ctx, const als_sparse *a, const void *G, float lambda, int f
     }
     const float *gram = ctx->gram[0];
     Plan *p = nullptr;
-    rc = get_plan(ctx, a, &p);
+    rc = get_plan(ctx, a, implicit, &p);
     if (rc != ALS_OK) return rc;
     rc = check_plan(ctx, a, p);
     if (rc != ALS_OK) return rc;
@@ -901,7 +916,7 @@ static int sum_over_entries(als_ctx *ctx, const als_sparse *csr, const float *X,
                             bool implicit, float alpha, double *sum_out) {
     int rc;
     Plan *p = nullptr;
-    rc = get_plan(ctx, csr, &p);
+    rc = get_plan(ctx, csr, implicit, &p);
     if (rc != ALS_OK) return rc;
     rc = check_plan(ctx, csr, p);
     if (rc != ALS_OK) return rc;
@@ -910,7 +925,7 @@ static int sum_over_entries(als_ctx *ctx, const als_sparse *csr, const float *X,
         if (ctx->fixed) return fail(ctx, ALS_EINVAL, "workspace too small for the partial sums of this matrix");
         if (ctx->sse_partial) { HIP_TRY(ctx, hipStreamSynchronize(ctx->stream)); HIP_TRY(ctx, hipFree(ctx->sse_partial)); }
         ctx->sse_partial = nullptr; ctx->sse_partial_bytes = 0;
-        HIP_TRY(ctx, hipMalloc(&ctx->sse_partial, need));
+        HIP_TRY(ctx, device_alloc(ctx, &ctx->sse_partial, need));
         ctx->sse_partial_bytes = need;
     }
     {
@@ -1154,6 +1169,7 @@ static int als_drop_plans_impl(als_ctx *ctx) {
     HIP_TRY(ctx, on_device.enter(ctx->cfg.device));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     for (auto &p : ctx->plans) free_plan(ctx, p);
+    free_sort_scratch(ctx);
     ctx->next_plan = 0;
     ctx->arena_used = 0;
     return ALS_OK;
