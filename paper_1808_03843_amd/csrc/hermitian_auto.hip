@@ -6,7 +6,7 @@
 // Why: fp32 MFMAs run at 1/16 of the rate of the 16-bit ones and share the issue port with the vector ALU, so the fp32
 // loop is bound by them (k_hermitian 112 of 141 TFLOP/s).  Two parts take 3 (77 MFMAs a step of 32 entries at
 // f = 100) where fp32 takes 8 x 28: Mid shape, CG(6), ms per sweep
-// f = 16 3.45 -> 2.18, 32 4.34 -> 2.67, 64 9.06 -> 5.40, 100 18.9 -> 11.5, 128 28.1 -> 16.1; 120,047 x 17,771 with 25M entries, exact,
+// f = 16 3.45 -> 2.18, 32 4.34 -> 2.67, 64 9.06 -> 5.40, 100 18.9 -> 11.3, 128 28.1 -> 16.1; 120,047 x 17,771 with 25M entries, exact,
 // f = 100 7.3 -> 5.0; the scan included.
 //
 // Accuracy.  A value s x = h + l + d has |d| <= 2^-22 |s x| (rounded to nearest twice: 2^-24 on average), or half the
@@ -38,7 +38,7 @@ __device__ __forceinline__ uint32_t rowmax16(uint32_t v) {
 // range[kRangeWide] = 1 if two fp16 parts would not do (see above; also for a NaN or an infinity anywhere, and for a
 // factor so small that its scale would be clamped).  range[kRangeWork ..) are zero between launches: the last
 // workgroup to finish reads them and clears them.  16 lanes per row with the lane -> feature map of the gathers, four
-// rows of a lane in flight.  Bound: one pass over the factor (192 MB: 120 us, 1.6 TB/s).
+// rows of a lane in flight.  Bound: one pass over the factor (192 MB: 92 us, 2.1 TB/s).
 template <int F>
 __global__ __launch_bounds__(256) void k_factor_range(const float *__restrict__ G, int64_t n, uint32_t *__restrict__ range) {
     constexpr int NT = tiles_1d(F), U = 4;

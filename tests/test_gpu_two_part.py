@@ -192,3 +192,27 @@ def test_replays_of_a_captured_half_sweep(P, mat):
     with torch.cuda.stream(side):
         als.synchronize()
         als.close()
+
+
+def test_explicit_and_implicit_calls_on_one_matrix_keep_their_own_work_items(P, mat):
+    """Default work items: 512 entries for explicit feedback at this size, 4096 for implicit feedback.  One context that
+    runs both in turn, and drops its plans in between, gives what contexts with those sizes set give, bit for bit."""
+    deg, ptr, idx, val = mat
+    f, m = 64, len(deg)
+    T = torch.from_numpy(_theta(f)).cuda()
+    sp = P.SparseMatrix.from_host(m, N, ptr, idx, np.abs(val))
+    def run(als):
+        X, Y = torch.zeros((m, f), device="cuda:0"), torch.zeros((m, f), device="cuda:0")
+        als.update_rows(sp, T, 0.3, X)
+        als.update_rows_implicit(sp, T, 0.3, 2.0, Y)
+        als.synchronize()
+        return X, Y, als.implicit_loss(sp, Y, T, 0.3, 2.0)
+    both, small, large = (P.Als(f, solver=P.SOLVER_CHOLESKY, chunk=c) for c in (0, 512, 4096))
+    want = run(small)[0], *run(large)[1:]
+    for _ in range(2):
+        got = run(both)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and got[2] == want[2]
+        both.csr_to_csc(sp)
+        both.drop_plans()
+    for als in (both, small, large):
+        als.close()
