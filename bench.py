@@ -81,8 +81,8 @@ def cpu_baseline(w, a_host, stride):
 TRAFFIC_SOURCE = "profiles/k_hermitian_mid_f100_cg6_counters.txt"
 MEASURED_TRAFFIC_BYTES_PER_LAUNCH = {
     ("mid", 100, "cg", 6, "f32", 4096): {
-        "k_hermitian": ((3.282e5 + 1.043e7) * 2048 + (2.86e5 + 5.569e5) * 1024) / 2,
-        "k_hermitian_cg": ((1.937e6 + 3.546e6) * 2048 + (4.125e4 + 5012) * 1024) / 2,
+        "k_hermitian": ((3.043e5 + 1.028e7) * 2048 + (2.86e5 + 5.569e5) * 1024) / 2,
+        "k_hermitian_cg": ((1.874e6 + 3.5e6) * 2048 + (4.125e4 + 5012) * 1024) / 2,
     },
 }
 
@@ -215,14 +215,16 @@ def main():
     # get_hermitian roofline.  Algorithmic flops = f*(f+1) per stored entry and half-sweep (lower triangle
     # of theta theta^T, FMA = 2).  Rows with >= chunk entries are built by k_hermitian into slots, shorter
     # rows by k_hermitian_cg (which also runs the solver: its time is charged to get_hermitian in full).
-    chunk = als.cfg.chunk or 4096
+    # default work items: 4096 entries, fewer for explicit feedback on matrices of 2^18 .. 2^25 entries
+    by_size = [(1 << 18, 4096), (1 << 21, 512), (1 << 23, 1024), (1 << 25, 2048)]
+    chunk = als.cfg.chunk or next((c for below, c in by_size if args.implicit is None and a.nnz < below), 4096)
     deg_r = np.diff(a.ptr)
     deg_c = np.bincount(a.idx, minlength=w.n)
     nnz_fit = int(a.nnz)   # entries the factors are fitted on (all of them unless --test-frac)
     nnz_slot = int(deg_r[deg_r >= chunk].sum() + deg_c[deg_c >= chunk].sum()) if (fused_n > 0 or short_n > 0) else 2 * nnz_fit
     # short rows run Algorithm 1 on their gathered rows and never form A_u (k_cg_gathered): their
     # entries are no get_hermitian work and are left out of its flops
-    short_limit = als.short_row_limit()   # 64, or 128 on the fp32 MFMA path at f = 100 / 128; 0: no such rows
+    short_limit = als.short_row_limit()   # 64, or 128 with fp32 factors at f = 100 / 128; 0: no such rows
     short_rows = int((deg_r < short_limit).sum() + (deg_c < short_limit).sum()) if short_n > 0 else 0
     nnz_short = int(deg_r[deg_r < short_limit].sum() + deg_c[deg_c < short_limit].sum()) if short_n > 0 else 0
     per_entry = w.f * (w.f + 1)
@@ -269,14 +271,17 @@ def main():
                                       "ms_per_sweep": (herm_ms + fused_ms) / K, "launches_per_sweep": launches,
                                       "flops_per_sweep": flops_sweep},
                 **kernels, **({"k_cg_gathered": short} if short else {})}
-    if args.factor_dtype in ("f32x3", "f32x2"):
+    # fp32 factors: explicit half-sweeps of matrices of 2^18 and more entries, in work items of up to 4096, run on the 16-bit
+    # matrix cores as two fp16 parts per value where the range of the factor allows it (always, for these workloads)
+    two_part = args.factor_dtype == "f32" and args.implicit is None and chunk <= 4096 and nnz_fit >= 1 << 18
+    if two_part or args.factor_dtype in ("f32x3", "f32x2"):
         # fp32 values as 16-bit parts on the 16-bit matrix cores: the numerator stays the algorithmic flops of the
         # fp32 Gram matrix, the denominator is the peak of the instruction that runs, the 16-bit dense MFMA peak
         for k in kernels.values():
             k["frac"] = k["tflops"] / PEAK_16BIT_MFMA_TFLOPS
             k["frac_of_fp32_mfma_peak"] = k["tflops"] / PEAK_FP32_MFMA_TFLOPS
         roofline.update({"peak": PEAK_16BIT_MFMA_TFLOPS, "frac": d["frac"],
-                         "note": "algorithmic fp32 flops against the 16-bit MFMA peak: six bf16 (f32x3) or three fp16 (f32x2) "
+                         "note": "algorithmic fp32 flops against the 16-bit MFMA peak: six bf16 (f32x3) or three fp16 (f32, f32x2) "
                                  "products per fp32 product, so the ceiling of the mode is 1/6 (1/3) of the 16-bit peak = "
                                  "417 (833) TFLOP/s of Gram work"})
         roofline["dominant_kernel"]["frac"] = d["frac"]
@@ -377,7 +382,7 @@ def main():
     out["measured_peaks"] = {"mfma_f32_TFLOPs": mf32 / 1e12, "mfma_bf16_TFLOPs": mbf16 / 1e12, "copy_GBps": cp / 1e9,
                              "note": "8 wavefronts per SIMD issuing independent MFMAs; copy of 1 GiB, bytes read + written"}
     if roofline["bound"] == "mfma":
-        reach = (mbf16 if args.factor_dtype in ("f32x3", "f32x2") else mf32) / 1e12
+        reach = (mbf16 if two_part or args.factor_dtype in ("f32x3", "f32x2") else mf32) / 1e12
         roofline["frac_of_measured_peak"] = roofline["achieved"] / reach
         roofline["all_get_hermitian"]["frac_of_measured_peak"] = roofline["all_get_hermitian"]["achieved"] / reach
     else:
